@@ -25,7 +25,8 @@
  *   - `stream` is a hipStream_t passed as void* (NULL = the null stream).  All
  *     device work is enqueued on it and the call returns without waiting,
  *     except ntc_get_device_error and ntc_kmeans_result, which synchronise
- *     the stream, and ntc_kmeans, which waits for its copy of a host array.
+ *     the stream, and ntc_kmeans with more than 256 groups, which waits for its
+ *     copy of a host array.
  *   - Calls on different streams are independent; two calls that share an
  *     output or workspace buffer must be ordered by the caller.
  *   - Arguments are validated on the host before anything is enqueued; on an
@@ -358,8 +359,8 @@ int ntc_divergence_map(const uint32_t *tex_id, int32_t width, int32_t height, in
  * may differ from another implementation's.
  *   features:  f32 [n][dim] (device), row-major
  *   init:      u32 [m] (HOST), distinct texture indices < n (the seeding is the
- *              caller's choice; the paper does not state one); copied to the
- *              device before the call returns (the call waits for `stream`)
+ *              caller's choice; the paper does not state one); read before the
+ *              call returns (with m > 256 the call waits for `stream`)
  *   assign:    u32 [n] (device, output)
  *   centroids: f64 [m][dim] (device, output)
  *   counts:    u32 [m] (device, output)
@@ -368,7 +369,8 @@ int ntc_divergence_map(const uint32_t *tex_id, int32_t width, int32_t height, in
  * Limits: 1 <= m <= min(n, NTC_MAX_DECODERS); n <= NTC_KMEANS_MAX_POINTS;
  * dim <= NTC_KMEANS_MAX_DIM; 1 <= max_iter <= NTC_KMEANS_MAX_ITER (else
  * NTC_ERR_ARG).  Work per iteration is O(n * m * dim) for the assignment and
- * O(m * n * dim) for the update (one workgroup per group scans all labels).
+ * O(m * n * dim / 64 + n * dim) for the update (one wave per group and 64
+ * dimensions lists the group's members).
  */
 #define NTC_KMEANS_MAX_POINTS (1 << 20)
 #define NTC_KMEANS_MAX_DIM 65536

@@ -126,7 +126,7 @@ template <int NL, int CH, int PE, int HID>
 int launch_decode_fma_shape(const DecodeArgs &a, hipStream_t stream);
 
 // k-means of per-texture features (ntc_cluster.hip).  Workspace: m seed
-// indices, then one u32 flag per iteration.
+// indices (m > 256 only), then one u32 flag word per iteration.
 size_t kmeans_workspace_bytes(int32_t m, int32_t max_iter);
 int launch_kmeans(const float *features, int32_t n, int32_t dim, int32_t m, const uint32_t *init,
                   int32_t max_iter, uint32_t *assign, double *centroids, uint32_t *counts,

@@ -68,6 +68,21 @@ def test_kmeans_matches_oracle(dev, oracle, seed, n, m, dim, spread):
     check(dev, oracle, f, seeds)
 
 
+@pytest.mark.parametrize("n,m,dim", [
+    (1, 1, 1), (3, 2, 63), (65, 9, 65),      # below and above one wave's dimensions
+    (1023, 8, 33), (1025, 7, 64),            # around one list of labels (1024)
+    (2500, 3, 65),                           # several lists, long member runs
+    (300, 256, 16), (300, 257, 16),          # both sides of the persistent path's group limit
+    (65536, 2, 4), (65537, 2, 4),            # and of its point limit
+])
+def test_kmeans_path_edges(dev, oracle, n, m, dim):
+    """The persistent launch and the launches per iteration at the edges of their
+    tiles and of the rule between them, bit for bit."""
+    f, _ = W.texture_features(100 + n, n, m, dim, spread=0.6)
+    say(f"[kmeans-edges] n={n} m={m} dim={dim}")
+    check(dev, oracle, f, W.kmeans_seeds(7, n, m), max_iter=12)
+
+
 def test_kmeans_hand_worked_and_ties(dev, oracle):
     say("[kmeans] 1-D hand-worked, ties and an empty group, unconverged stop")
     g = check(dev, oracle, np.array([[0.0], [1.0], [10.0], [11.0]], np.float32), [0, 1])
