@@ -11,26 +11,33 @@
 // Work unit: one wave, one tile of 64 queries (lane l owns query slot l).
 //
 // Layer math: the layer output H^T = W X^T is computed with
-// v_mfma_f32_32x32x16_f16, weights as the A operand (rows = output units) and
-// the activations of 32 queries as the B operand (columns = queries); a tile is
-// two such 32-query column blocks.  Each lane holds, for its column, 8 K-values
-// of A and of B per instruction (half h = lane / 32 holds K-values 8h .. 8h+7 of
-// a 16-wide K-slice) and 16 fp32 results: rows 8g + 4h + r (register 4g + r).
-// Those 16 results, converted to fp16, are directly the B operand of the next
-// layer once the next layer's weight columns are permuted: inside every
-// 16-wide K-slice, logical K-position kappa reads hidden unit sigma(kappa), sigma
-// swapping bits 2 and 3.  The permutation is applied when the weights are
-// staged into LDS, so no activation ever leaves registers.  Biases enter as the
-// accumulator input of the first MFMA of each layer.
+// v_mfma_f32_16x16x32_f16, weights as the A operand (rows = output units) and
+// the activations of 16 queries as the B operand (columns = queries); a tile is
+// four such column blocks.  Lane l = (g = l / 16, n = l % 16): the B operand of
+// column block j (queries 16j .. 16j+15) holds K-values 8g .. 8g+7 of query
+// 16j + n, the A operand row n with the same K-values, the accumulator rows
+// 4g .. 4g+3 of column n.  Converted to fp16, the accumulators of row blocks 2t
+// and 2t+1 are directly the next layer's B operand for K-step t once that
+// layer's weight columns are permuted (position 8g + e reads unit 32t + 4g + e
+// for e < 4 and 32t + 16 + 4g + e - 4 otherwise); the permutation is applied
+// when the weights are loaded, so activations never leave registers.  Biases
+// are the accumulator input of the first MFMA of each row block.  Every kernel
+// runs this one function (mlp), so binned and stream mode give the same bits.
 //
-// Decoder weights live in LDS, pre-arranged so that each lane reads its 8
-// fp16 A-values of a fragment with one 16-byte load.  Binned mode: a workgroup
-// walks a contiguous range of 64-slot tiles of the permutation, four tiles at a
-// time (one per wave) inside one bin, restaging weights only when the bin
-// changes.  Stream mode: a workgroup takes 4 consecutive tiles, computes the
-// features once, then loops over the distinct decoders present; every wave
-// that holds queries of that decoder runs its full MLP and keeps the results
-// of those lanes only.
+// Why 16x16x32: the decode draws the chip into its power limit (1.7-1.9 GHz
+// measured inside the 4K clustered decode, 2.1 without its MFMAs or its LDS
+// weight reads), so its time follows the energy of a tile.  16x16x32 moves half
+// the accumulator bytes per flop of 32x32x16 and pads an 8-wide output layer to
+// 16 rows instead of 32: 161 -> 153 us on the 4K clustered frame, 50.7 -> 48 us
+// on the 1080p one.
+//
+// Decoders with 64-wide hidden layers keep their weights in registers (14
+// fragments of 4 registers for 32-64-64-8), two waves per SIMD: no LDS reads
+// but the biases, no barriers, and the taps of the next tile are fetched a
+// whole MLP ahead.  Against weights read from LDS for every tile, four waves per
+// SIMD: 153 -> 148-151 us on the 4K clustered frame, 48 -> 45 us on the 1080p
+// one, 58 -> 52 us on the divergent one.  128-wide decoders (84 fragments for
+// 48-128-128-128-8) are staged in LDS, one image per workgroup.
 //
 // A second engine (decode_fma, end of the file) evaluates the MLP per lane with
 // vector dot products instead: the paper's Non-Shared FMA comparison.
@@ -41,7 +48,6 @@ namespace {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float float2v __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -59,168 +65,188 @@ __device__ __forceinline__ uint32_t pack_half2(float a, float b) {
 
 __device__ __forceinline__ half8 as_half8(u32x4 v) { return __builtin_bit_cast(half8, v); }
 
-__device__ __forceinline__ floatx16 mfma(half8 a, half8 b, floatx16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
-}
-
-// Logical K-position inside a 16-wide slice -> hidden unit that the previous
-// layer's accumulator layout places there.
-__device__ __forceinline__ int sigma16(int k) {
-  return (k & ~0xC) | ((k & 4) << 1) | ((k & 8) >> 1);
+__device__ __forceinline__ floatx4 mfma16(half8 a, half8 b, floatx4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
 
 template <int NL, int CH, int PE, int HID>
 struct Shape {
   static constexpr int FL = NL * CH;         // latent features per query
   static constexpr int F = FL + PE;          // + positional-encoding features
-  static constexpr int KS0 = F / 16;         // K-slices of layer 0
-  static constexpr int MB = HID / 32;        // 32-row output blocks of a hidden layer
-  static constexpr int KSH = HID / 16;       // K-slices of a layer fed by a hidden layer
+  static constexpr int KS0 = (F + 31) / 32;  // 32-wide K-steps of layer 0 (zero padded)
+  static constexpr int MB = HID / 16;        // 16-row blocks of a hidden layer
+  static constexpr int KSH = HID / 32;       // K-steps of a layer fed by a hidden layer
   static_assert(F % 16 == 0, "feature count must be a multiple of 16");
   static_assert(HID % 32 == 0, "hidden width must be a multiple of 32");
   static_assert(CH == 8 || CH == 16, "8 or 16 channels per level");
-  static_assert(PE % 16 == 0, "positional features come in whole K-slices");
+  static_assert(PE % 16 == 0, "positional features come in whole 16-byte pieces");
 };
 
-// LDS image of one decoder: A fragments (64 lanes x 16 B each), then fp32
-// biases (rows padded to 32 per block).
-struct Image {
-  int n_frags;    // fragments
-  int bias_off;   // float offset of the biases inside the image (after fragments)
-  int n_bias;     // floats
-  int bytes;
-};
-
-template <int NL, int CH, int PE, int HID>
-__host__ __device__ inline Image image_of(int n_hidden) {
+// One decoder as A fragments (64 lanes x 16 bytes each: layer 0 by row block,
+// then K-step; every hidden layer the same; the output layer's one row block)
+// and fp32 biases (HID per hidden activation, then 16 of the output layer).
+template <int NL, int CH, int PE, int HID, int NH>
+struct Net {
   using S = Shape<NL, CH, PE, HID>;
-  Image im;
-  im.n_frags = S::MB * S::KS0 + n_hidden * S::MB * S::KSH + S::KSH;
-  im.bias_off = im.n_frags * 256;  // 1024 B = 256 floats per fragment
-  im.n_bias = HID * (1 + n_hidden) + 32;
-  im.bytes = (im.bias_off + im.n_bias) * 4;
-  return im;
-}
-
-// Source of lane-slice lf of the image: the layer's weight block and the row,
-// K-slice, half and shape that select its 8 weights.
-template <int NL, int CH, int PE, int HID>
-struct SliceSource {
-  size_t woff;  // offset of W_layer inside the decoder's parameter block
-  int layer, row, s, h, din, dout;
-};
-
-template <int NL, int CH, int PE, int HID>
-__device__ __forceinline__ SliceSource<NL, CH, PE, HID> slice_source(const DecodeArgs &a, int lf) {
-  using S = Shape<NL, CH, PE, HID>;
-  SliceSource<NL, CH, PE, HID> r;
-  const int f = lf / kWave, lane = lf % kWave;
-  int mb;
-  if (f < S::MB * S::KS0) {
-    r.layer = 0; mb = f / S::KS0; r.s = f % S::KS0; r.din = S::F; r.dout = HID;
-  } else if (f < S::MB * S::KS0 + a.n_hidden * S::MB * S::KSH) {
-    const int g = f - S::MB * S::KS0;
-    r.layer = 1 + g / (S::MB * S::KSH);
-    const int q = g % (S::MB * S::KSH);
-    mb = q / S::KSH; r.s = q % S::KSH; r.din = HID; r.dout = HID;
-  } else {
-    r.layer = a.n_hidden + 1; mb = 0; r.s = f - S::MB * S::KS0 - a.n_hidden * S::MB * S::KSH;
-    r.din = HID; r.dout = a.out_dim;
+  static constexpr int kHidden0 = S::MB * S::KS0;                // first hidden fragment
+  static constexpr int kOut0 = kHidden0 + NH * S::MB * S::KSH;   // first output fragment
+  static constexpr int kFrags = kOut0 + S::KSH;
+  static constexpr int kBiases = HID * (1 + NH) + 16;
+  static constexpr int kBiasOff = kFrags * 256;                  // words, inside the LDS image
+  static constexpr int kImageBytes = (kBiasOff + kBiases) * 4;
+  // offset (values) of layer l's weights inside the decoder's block
+  static __host__ __device__ constexpr int layer_off(int l) {
+    return l == 0 ? 0 : HID * (S::F + 1) + (l - 1) * HID * (HID + 1);
   }
-  r.woff = r.layer == 0 ? 0 : (size_t)HID * (S::F + 1) + (size_t)(r.layer - 1) * HID * (HID + 1);
-  r.row = mb * 32 + (lane & 31);
-  r.h = lane >> 5;
-  return r;
-}
 
-// Weight unit that element e of a lane-slice holds (layer 0 reads the
-// features in order; later layers read the previous layer's accumulator
-// order, see sigma16).
-template <int NL, int CH, int PE, int HID>
-__device__ __forceinline__ int slice_unit(const SliceSource<NL, CH, PE, HID> &r, int e) {
-  const int kap = 8 * r.h + e;
-  return 16 * r.s + (r.layer == 0 ? kap : sigma16(kap));
-}
-
-// Copies decoder `dec` into the LDS image, re-arranged into A fragments; all
-// threads of the workgroup take part; the caller brackets it with barriers.
-// The decoder block is read through a raw buffer resource: 32-bit offsets, and
-// a weight outside its layer (padding rows and columns) gets an offset past
-// the block, which the hardware returns as zero.  A thread issues the loads of
-// kStageSlices lane-slices (8 weights each) back to back, so staging costs one
-// memory round trip per kStageSlices * THREADS lane-slices.
-constexpr int kStageSlices = 2;
-constexpr uint32_t kPastBlock = 0xFFFFFF00u;  // byte offset past any decoder block
-
-template <int NL, int CH, int PE, int HID, int THREADS>
-__device__ void stage_decoder(const DecodeArgs &a, uint32_t dec, uint32_t *lds) {
-  const Image im = image_of<NL, CH, PE, HID>(a.n_hidden);
-  const uint16_t *p = a.params + (size_t)dec * (size_t)a.dec_stride;
-  const __amdgpu_buffer_rsrc_t rsrc =
-      __builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)(a.dec_stride * 2), 0x00020000);
-  const int n_layers = a.n_hidden + 2;
-  const int n_slices = im.n_frags * kWave;
-  for (int base = threadIdx.x; base < n_slices; base += kStageSlices * THREADS) {
-    uint32_t v[kStageSlices][8];
-#pragma unroll
-    for (int i = 0; i < kStageSlices; ++i) {
-      const int lf = base + i * THREADS;
-      const SliceSource<NL, CH, PE, HID> r = slice_source<NL, CH, PE, HID>(a, lf < n_slices ? lf : 0);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const int unit = slice_unit(r, e);
-        const bool in = r.row < r.dout && unit < r.din;
-        const uint32_t off = in ? (uint32_t)(r.woff + (size_t)r.row * r.din + unit) * 2u : kPastBlock;
-        v[i][e] = __builtin_amdgcn_raw_buffer_load_b16(rsrc, off, 0, 0);
-      }
+  // Lane's 8 weights of fragment f, straight from the decoder's parameter block
+  // p: one 16-byte load for layer 0 (units 32s + 8g ..), two 8-byte loads for
+  // the others (the order the previous layer's accumulators leave its outputs
+  // in).  The block is only 2-byte aligned in general (an odd output width), which
+  // these loads allow.  Rows past the output width and units past the features
+  // read weight 0 of the block and become zero.
+  struct __attribute__((packed, aligned(2))) Piece16 { u32x4 v; };
+  struct __attribute__((packed, aligned(2))) Piece8 { u32x2 v; };
+  static __device__ __forceinline__ half8 load_slice(const uint16_t *p, int out_dim, int f,
+                                                     int lane) {
+    const int g = lane >> 4, n = lane & 15;
+    if (f < kHidden0) {
+      const int row = 16 * (f / S::KS0) + n, unit = 32 * (f % S::KS0) + 8 * g;
+      const bool in = S::F % 32 == 0 || unit < S::F;
+      const u32x4 v = ((const Piece16 *)(p + (in ? row * S::F + unit : 0)))->v;
+      return as_half8(in ? v : u32x4{0u, 0u, 0u, 0u});
     }
-#pragma unroll
-    for (int i = 0; i < kStageSlices; ++i) {
-      const int lf = base + i * THREADS;
-      if (lf < n_slices) {
-        const u32x4 packed = {v[i][0] | v[i][1] << 16, v[i][2] | v[i][3] << 16,
-                              v[i][4] | v[i][5] << 16, v[i][6] | v[i][7] << 16};
-        *(u32x4 *)(lds + (size_t)(lf / kWave) * 256 + (lf % kWave) * 4) = packed;
-      }
-    }
-  }
-  // biases, converted to fp32; rows past the layer width read zero, as above
-  using S = Shape<NL, CH, PE, HID>;
-  float *bias = (float *)(lds + im.bias_off);
-  for (int i = threadIdx.x; i < im.n_bias; i += THREADS) {
-    int layer, row, dout;
-    if (i < HID * (1 + a.n_hidden)) {
-      layer = i / HID; row = i % HID; dout = HID;
+    int row, s, off;
+    bool in = true;
+    if (f < kOut0) {
+      const int q = f - kHidden0, layer = q / (S::MB * S::KSH), r = q % (S::MB * S::KSH);
+      row = 16 * (r / S::KSH) + n;
+      s = r % S::KSH;
+      off = layer_off(1 + layer);
     } else {
-      layer = n_layers - 1; row = i - HID * (1 + a.n_hidden); dout = a.out_dim;
+      row = n;
+      s = f - kOut0;
+      off = layer_off(1 + NH);
+      in = n < out_dim;
     }
-    const size_t off =
-        layer == 0 ? 0 : (size_t)HID * (S::F + 1) + (size_t)(layer - 1) * HID * (HID + 1);
-    const int din = layer == 0 ? S::F : HID;
-    const uint32_t boff = row < dout ? (uint32_t)(off + (size_t)dout * din + row) * 2u : kPastBlock;
-    const uint16_t hb = __builtin_amdgcn_raw_buffer_load_b16(rsrc, boff, 0, 0);
+    const uint16_t *src = p + (in ? off + row * HID + 32 * s + 4 * g : 0);
+    const u32x2 lo = ((const Piece8 *)src)->v, hi = ((const Piece8 *)(src + 16))->v;
+    return as_half8(in ? u32x4{lo[0], lo[1], hi[0], hi[1]} : u32x4{0u, 0u, 0u, 0u});
+  }
+
+  // Bias i of the image; the output layer's are scaled by -log2(e), so that
+  // the sigmoid's exponent is one multiply-add, and zero past its width.
+  static __device__ __forceinline__ float load_bias(const uint16_t *p, int out_dim, int i) {
+    const bool out = i >= HID * (1 + NH);
+    const int l = out ? 1 + NH : i / HID, row = out ? i - HID * (1 + NH) : i % HID;
+    const bool in = !out || row < out_dim;
+    const int dout = out ? out_dim : HID, din = l == 0 ? S::F : HID;
+    const uint16_t hb = p[in ? layer_off(l) + dout * din + row : 0];
     const float v = (float)__builtin_bit_cast(_Float16, hb);
-    bias[i] = layer == n_layers - 1 ? v * -kLog2e : v;
+    return !in ? 0.f : out ? v * -kLog2e : v;
   }
-}
+};
 
-// 16 bias values of output block `mb` of a layer, in accumulator order.
-__device__ __forceinline__ floatx16 bias_frag(const float *bias_layer, int mb) {
-  const int h = lane_id() >> 5;
-  floatx16 c;
+// A decoder read from its LDS image.
+template <int NL, int CH, int PE, int HID, int NH>
+struct LdsNet : Net<NL, CH, PE, HID, NH> {
+  using N = Net<NL, CH, PE, HID, NH>;
+  const uint32_t *lds;
+  __device__ __forceinline__ half8 weight(int f) const {
+    return as_half8(*(const u32x4 *)(lds + (size_t)f * 256 + lane_id() * 4));
+  }
+  __device__ __forceinline__ const float *biases() const {
+    return (const float *)lds + N::kBiasOff;
+  }
+};
+
+// A decoder whose weights this wave holds in registers and whose biases lie in
+// the wave's own LDS region.
+template <int NL, int CH, int PE, int HID, int NH>
+struct RegNet : Net<NL, CH, PE, HID, NH> {
+  using N = Net<NL, CH, PE, HID, NH>;
+  half8 w[N::kFrags];
+  float *lds;  // N::kBiases floats
+  __device__ __forceinline__ half8 weight(int f) const { return w[f]; }
+  __device__ __forceinline__ const float *biases() const { return lds; }
+  // Loads decoder `dec`: every load is issued before any is used.
+  __device__ __forceinline__ void load(const DecodeArgs &a, uint32_t dec) {
+    const uint16_t *p = a.params + (size_t)dec * (size_t)a.dec_stride;
+    const int lane = (int)lane_id();
+    constexpr int kPer = (N::kBiases + kWave - 1) / kWave;
+    float b[kPer];
 #pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    const floatx4 v = *(const floatx4 *)(bias_layer + mb * 32 + 8 * g + 4 * h);
-    c[4 * g + 0] = v[0];
-    c[4 * g + 1] = v[1];
-    c[4 * g + 2] = v[2];
-    c[4 * g + 3] = v[3];
+    for (int i = 0; i < kPer; ++i) {
+      const int k = i * kWave + lane;
+      b[i] = N::load_bias(p, a.out_dim, k < N::kBiases ? k : 0);
+    }
+#pragma unroll
+    for (int f = 0; f < N::kFrags; ++f) w[f] = N::load_slice(p, a.out_dim, f, lane);
+    // every fragment has arrived when this returns: a load left pending into
+    // the caller's loop would be waited for on the path that loads nothing
+#pragma unroll
+    for (int f = 0; f < N::kFrags; ++f) {
+      u32x4 v = __builtin_bit_cast(u32x4, w[f]);
+      asm volatile("" : "+v"(v));
+      w[f] = as_half8(v);
+    }
+    // the wave's earlier reads of the region come before these writes, and its
+    // later ones after: a wave's LDS operations execute in order
+#pragma unroll
+    for (int i = 0; i < kPer; ++i) {
+      const int k = i * kWave + lane;
+      if (k < N::kBiases) lds[k] = b[i];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
-  return c;
-}
+};
 
-__device__ __forceinline__ half8 a_frag(const uint32_t *lds, int f) {
-  return as_half8(*(const u32x4 *)(lds + (size_t)f * 256 + lane_id() * 4));
+// A decoder read straight from its parameter block, fragment by fragment
+// (stream mode of 128-wide decoders), biases in the wave's own LDS region.
+template <int NL, int CH, int PE, int HID, int NH>
+struct DirectNet : Net<NL, CH, PE, HID, NH> {
+  using N = Net<NL, CH, PE, HID, NH>;
+  const uint16_t *p;
+  int out_dim;
+  float *lds;
+  __device__ __forceinline__ half8 weight(int f) const {
+    return N::load_slice(p, out_dim, f, (int)lane_id());
+  }
+  __device__ __forceinline__ const float *biases() const { return lds; }
+  __device__ __forceinline__ void open(const DecodeArgs &a, uint32_t dec) {
+    p = a.params + (size_t)dec * (size_t)a.dec_stride;
+    out_dim = a.out_dim;
+    for (int i = (int)lane_id(); i < N::kBiases; i += kWave) lds[i] = N::load_bias(p, out_dim, i);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+};
+
+// Copies decoder `dec` into the LDS image; all threads of the workgroup take
+// part and the caller brackets it with barriers.  A thread issues the loads of
+// kStageSlices lane-slices back to back.
+constexpr int kStageSlices = 4;
+
+template <typename N, int THREADS>
+__device__ void stage_decoder(const DecodeArgs &a, uint32_t dec, uint32_t *lds) {
+  const uint16_t *p = a.params + (size_t)dec * (size_t)a.dec_stride;
+  constexpr int kSlices = N::kFrags * kWave;
+  for (int base = threadIdx.x; base < kSlices; base += kStageSlices * THREADS) {
+    half8 v[kStageSlices];
+#pragma unroll
+    for (int i = 0; i < kStageSlices; ++i) {
+      const int lf = base + i * THREADS;
+      v[i] = N::load_slice(p, a.out_dim, (lf < kSlices ? lf : base) / kWave, lf % kWave);
+    }
+#pragma unroll
+    for (int i = 0; i < kStageSlices; ++i) {
+      const int lf = base + i * THREADS;
+      if (lf < kSlices) *(half8 *)(lds + (size_t)lf * 4) = v[i];
+    }
+  }
+  float *bias = (float *)lds + N::kBiasOff;
+  for (int i = threadIdx.x; i < N::kBiases; i += THREADS) bias[i] = N::load_bias(p, a.out_dim, i);
 }
 
 // Positional encoding of the query's texture coordinate, PE / 4 octaves k:
@@ -390,27 +416,39 @@ __device__ __forceinline__ void interp_taps(const TileTaps<NL, CH> &T,
   for (int l = 0; l < NL; ++l) interp_level_h2<CH>(T.lv[l], x + l * CH / 2);
 }
 
-// Exchange halves between lane l and lane l ^ 32 so that, per 16-wide K-slice,
-// b0 holds the slice for column block 0 (queries of lanes 0..31) and b1 for
-// column block 1 (queries of lanes 32..63), each lane holding K-values 8h..8h+7.
-// v_permlane32_swap(lo, hi) moves lanes 0..31 of hi into lanes 32..63 of lo and
-// lanes 32..63 of lo into lanes 0..31 of hi: afterwards lo is the column-block-0
-// operand and hi the column-block-1 operand in every lane.
-template <int KS>
-__device__ __forceinline__ void to_b_operands(const uint32_t (&x)[KS * 8], half8 (&b0)[KS],
-                                              half8 (&b1)[KS]) {
+// B operands of layer 0 from the features of the lane's own query (lane =
+// query slot; x[c/2] holds features c, c+1): a 4x4 transpose of (16-lane row,
+// 8-feature group) blocks per K-step, one v_permlane32_swap stage and one
+// v_permlane16_swap stage.  Afterwards xb[j][s] holds, in lane (g, n),
+// features 32s + 8g .. +7 of query 16j + n.
+template <int KS0, int XW>
+__device__ __forceinline__ void to_b16(const uint32_t (&x)[XW], half8 (&xb)[4][KS0]) {
 #pragma unroll
-  for (int s = 0; s < KS; ++s) {
-    u32x4 v0, v1;
+  for (int s = 0; s < KS0; ++s) {
+    uint32_t e[4][4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const auto r = __builtin_amdgcn_permlane32_swap(x[8 * s + i], x[8 * s + 4 + i], false,
-                                                      false);
-      v0[i] = r[0];
-      v1[i] = r[1];
+    for (int g = 0; g < 4; ++g)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int w = 16 * s + 4 * g + v;
+        e[g][v] = w < XW ? x[w] : 0u;
+      }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const auto a = __builtin_amdgcn_permlane32_swap(e[0][v], e[2][v], false, false);
+      const auto b = __builtin_amdgcn_permlane32_swap(e[1][v], e[3][v], false, false);
+      e[0][v] = a[0]; e[2][v] = a[1];
+      e[1][v] = b[0]; e[3][v] = b[1];
     }
-    b0[s] = as_half8(v0);
-    b1[s] = as_half8(v1);
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const auto a = __builtin_amdgcn_permlane16_swap(e[0][v], e[1][v], false, false);
+      const auto b = __builtin_amdgcn_permlane16_swap(e[2][v], e[3][v], false, false);
+      e[0][v] = a[0]; e[1][v] = a[1];
+      e[2][v] = b[0]; e[3][v] = b[1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) xb[j][s] = as_half8(u32x4{e[j][0], e[j][1], e[j][2], e[j][3]});
   }
 }
 
@@ -430,25 +468,18 @@ __device__ __forceinline__ uint32_t leaky_pack2(float a, float b, uint32_t slope
   return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(h, h * s));
 }
 
-// Hidden activation + fp16 of one 32-row output block -> two K-slices of the
-// next layer.  LEAKY selects LeakyReLU; it is a template parameter so that the
-// layer's MFMAs and conversions stay in one basic block.
+// Hidden activation and fp16 of row blocks 2t (lo) and 2t+1 (hi): the next
+// layer's B operand for K-step t.
 template <bool LEAKY>
-__device__ __forceinline__ void relu_pack(const floatx16 &acc, half8 &s0, half8 &s1,
-                                          uint32_t slope_h2) {
-  u32x4 a, b;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if constexpr (LEAKY) {
-      a[i] = leaky_pack2(acc[2 * i], acc[2 * i + 1], slope_h2);
-      b[i] = leaky_pack2(acc[8 + 2 * i], acc[8 + 2 * i + 1], slope_h2);
-    } else {
-      a[i] = relu_pack2(acc[2 * i], acc[2 * i + 1]);
-      b[i] = relu_pack2(acc[8 + 2 * i], acc[8 + 2 * i + 1]);
-    }
+__device__ __forceinline__ half8 act_pack16(const floatx4 &lo, const floatx4 &hi,
+                                            uint32_t slope_h2) {
+  if constexpr (LEAKY) {
+    return as_half8(u32x4{leaky_pack2(lo[0], lo[1], slope_h2), leaky_pack2(lo[2], lo[3], slope_h2),
+                          leaky_pack2(hi[0], hi[1], slope_h2), leaky_pack2(hi[2], hi[3], slope_h2)});
+  } else {
+    return as_half8(u32x4{relu_pack2(lo[0], lo[1]), relu_pack2(lo[2], lo[3]),
+                          relu_pack2(hi[0], hi[1]), relu_pack2(hi[2], hi[3])});
   }
-  s0 = as_half8(a);
-  s1 = as_half8(b);
 }
 
 // 1 / (1 + exp(-(z + b))) with nb = -b * log2(e).
@@ -456,75 +487,73 @@ __device__ __forceinline__ float sigmoid(float z, float nb) {
   return __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(__builtin_fmaf(z, -kLog2e, nb)));
 }
 
-// Runs the staged decoder on the tile's features; returns the output layer's
-// accumulators (sigmoid applied) for the two column blocks.
-template <int NL, int CH, int PE, int HID, int NH, bool LEAKY>
-__device__ __forceinline__ void run_mlp(const uint32_t *lds,
-                                        const half8 (&xb0)[(NL * CH + PE) / 16],
-                                        const half8 (&xb1)[(NL * CH + PE) / 16], floatx16 &y0,
-                                        floatx16 &y1, uint32_t slope_h2) {
-  using S = Shape<NL, CH, PE, HID>;
-  const float *bias = (const float *)(lds) + image_of<NL, CH, PE, HID>(NH).bias_off;
-  half8 h0[S::KSH], h1[S::KSH];
-  // layer 0: F -> HID
+// Two row blocks (2t, 2t+1) of a layer on the four column blocks, activated and
+// converted: the next layer's B operand for K-step t.  KS K-steps, fragments
+// from f0, biases of the two blocks at b.
+template <int KS, bool LEAKY, typename NET>
+__device__ __forceinline__ void row_pair(const NET &net, int f0, const float *b,
+                                         const half8 (&x)[4][KS], half8 (&o)[4],
+                                         uint32_t slope_h2) {
+  const uint32_t g = lane_id() >> 4;
+  const floatx4 blo = *(const floatx4 *)(b + 4 * g), bhi = *(const floatx4 *)(b + 16 + 4 * g);
+  floatx4 lo[4], hi[4];
 #pragma unroll
-  for (int mb = 0; mb < S::MB; ++mb) {
-    floatx16 c0 = bias_frag(bias, mb), c1 = c0;
+  for (int s = 0; s < KS; ++s) {
+    const half8 wlo = net.weight(f0 + s), whi = net.weight(f0 + KS + s);
 #pragma unroll
-    for (int s = 0; s < S::KS0; ++s) {
-      const half8 w = a_frag(lds, mb * S::KS0 + s);
-      c0 = mfma(w, xb0[s], c0);
-      c1 = mfma(w, xb1[s], c1);
-    }
-    relu_pack<LEAKY>(c0, h0[2 * mb], h0[2 * mb + 1], slope_h2);
-    relu_pack<LEAKY>(c1, h1[2 * mb], h1[2 * mb + 1], slope_h2);
+    for (int j = 0; j < 4; ++j) lo[j] = mfma16(wlo, x[j][s], s == 0 ? blo : lo[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) hi[j] = mfma16(whi, x[j][s], s == 0 ? bhi : hi[j]);
   }
-  int frag = S::MB * S::KS0;
-  const float *bl = bias + HID;
-  // hidden -> hidden
 #pragma unroll
-  for (int layer = 0; layer < NH; ++layer) {
-    half8 n0[S::KSH], n1[S::KSH];
-#pragma unroll
-    for (int mb = 0; mb < S::MB; ++mb) {
-      floatx16 c0 = bias_frag(bl, mb), c1 = c0;
-#pragma unroll
-      for (int s = 0; s < S::KSH; ++s) {
-        const half8 w = a_frag(lds, frag + mb * S::KSH + s);
-        c0 = mfma(w, h0[s], c0);
-        c1 = mfma(w, h1[s], c1);
-      }
-      relu_pack<LEAKY>(c0, n0[2 * mb], n0[2 * mb + 1], slope_h2);
-      relu_pack<LEAKY>(c1, n1[2 * mb], n1[2 * mb + 1], slope_h2);
-    }
-#pragma unroll
-    for (int s = 0; s < S::KSH; ++s) {
-      h0[s] = n0[s];
-      h1[s] = n1[s];
-    }
-    frag += S::MB * S::KSH;
-    bl += HID;
-  }
-  // output layer: HID -> out (rows padded to 32 with zero weights).  Its
-  // accumulators start at zero (an inline constant); the bias is added by the
-  // sigmoid, which needs one multiply-add per value anyway.
-  floatx16 c0 = {}, c1 = {};
-#pragma unroll
-  for (int s = 0; s < S::KSH; ++s) {
-    const half8 w = a_frag(lds, frag + s);
-    c0 = mfma(w, h0[s], c0);
-    c1 = mfma(w, h1[s], c1);
-  }
-  y0 = c0;
-  y1 = c1;
+  for (int j = 0; j < 4; ++j) o[j] = act_pack16<LEAKY>(lo[j], hi[j], slope_h2);
 }
 
-// Output-layer biases of this lane's rows 4h..4h+3, pre-scaled by -log2(e)
-// when the decoder is staged (the sigmoid's exponent is then one fma).
-template <int NL, int CH, int PE, int HID, int NH>
-__device__ __forceinline__ floatx4 out_bias(const uint32_t *lds, int first_row) {
-  const float *b = (const float *)(lds) + image_of<NL, CH, PE, HID>(NH).bias_off + HID * (1 + NH);
-  return *(const floatx4 *)(b + first_row + 4 * (lane_id() >> 5));
+// Runs a decoder on the tile's features (B operands); y[j] holds the output
+// layer's accumulators of column block j, bias not yet added.  The output layer
+// takes each K-step as the last hidden layer produces it, so that layer's
+// outputs are never all live.
+template <int NL, int CH, int PE, int HID, int NH, bool LEAKY, typename NET>
+__device__ __forceinline__ void mlp(const NET &net,
+                                    const half8 (&xb)[4][Shape<NL, CH, PE, HID>::KS0],
+                                    floatx4 (&y)[4], uint32_t slope_h2) {
+  using S = Shape<NL, CH, PE, HID>;
+  using N = Net<NL, CH, PE, HID, NH>;
+  static_assert(NH >= 1, "a hidden -> hidden layer feeds the output layer");
+  const float *bias = net.biases();
+  half8 h[4][S::KSH];
+#pragma unroll
+  for (int t = 0; t < S::KSH; ++t) {
+    half8 o[4];
+    row_pair<S::KS0, LEAKY>(net, 2 * t * S::KS0, bias + 32 * t, xb, o, slope_h2);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) h[j][t] = o[j];
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) y[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int layer = 0; layer < NH; ++layer) {
+    half8 m[4][S::KSH];
+#pragma unroll
+    for (int t = 0; t < S::KSH; ++t) {
+      half8 o[4];
+      row_pair<S::KSH, LEAKY>(net, N::kHidden0 + layer * S::MB * S::KSH + 2 * t * S::KSH,
+                              bias + HID * (1 + layer) + 32 * t, h, o, slope_h2);
+      if (layer == NH - 1) {
+        const half8 w = net.weight(N::kOut0 + t);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) y[j] = mfma16(w, o[j], y[j]);
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) m[j][t] = o[j];
+      }
+    }
+    if (layer < NH - 1)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int t = 0; t < S::KSH; ++t) h[j][t] = m[j][t];
+  }
 }
 
 // Raw buffer resource over the output rows: a store whose byte offset lies past
@@ -539,53 +568,23 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t out_resource(const DecodeArgs 
   return __builtin_amdgcn_make_buffer_rsrc(a.out, 0, (int)bytes, 0x00020000);
 }
 
-// How a column block's rows reach memory: for an output width of 4 or 8, one
-// fp32 (or fp16) run of the 4 rows each lane holds; for a width of 3 (RGB rows,
-// the Sec. 4 setup) the lanes holding rows 0..3 store rows 0..2 (fp32: one
-// 12-byte store; fp16: a 4-byte and a 2-byte store); for any other width up to
-// 16, one store per row.
+// How a query's rows reach memory: for an output width of 4 or 8, one fp32 (or
+// fp16) run of the 4 rows each lane holds; for a width of 3 (RGB rows, the
+// Sec. 4 setup) the lanes holding rows 0..3 store rows 0..2 (fp32: one 12-byte
+// store; fp16: a 4-byte and a 2-byte store); for any other width, one store per
+// row (kStoreEach up to 8 rows, kStoreEachWide up to 16).
 enum StoreMode { kStoreF32x4 = 0, kStoreF16x4 = 1, kStoreEach = 2, kStoreF32x3 = 3,
-                 kStoreF16x3 = 4 };
+                 kStoreF16x3 = 4, kStoreEachWide = 5 };
 
-// Store instructions per 32-query column block; fixed for a mode, so the wait
-// counts of the software pipeline do not depend on the data.
+// Widths past 8 need the accumulator rows 8..15.
 template <int STORE>
-constexpr int kStoresPerBlock = STORE == kStoreEach ? 8 : STORE == kStoreF16x3 ? 2 : 1;
+constexpr bool kWideRows = STORE == kStoreEachWide;
 
-// Decoded values this lane stores for one 32-query column block: rows 4h..4h+3
-// (lo) and 8+4h..8+4h+3 (hi) of the query in its column, after the sigmoid, as
-// fp32 bits.  hi exists only in the per-row mode and is computed only when the
-// width reaches it (otherwise its stores are dropped and its value is unused).
-struct OutRows {
-  u32x4 lo, hi;
-};
-
-// Scaled output biases (see out_bias) of the lane's lo and hi rows.
-struct OutBias {
-  floatx4 lo, hi;
-};
-
-template <int NL, int CH, int PE, int HID, int NH, int STORE>
-__device__ __forceinline__ OutBias load_out_bias(const uint32_t *lds, int out_dim) {
-  OutBias b;
-  b.lo = out_bias<NL, CH, PE, HID, NH>(lds, 0);
-  b.hi = STORE == kStoreEach && out_dim > 8 ? out_bias<NL, CH, PE, HID, NH>(lds, 8) : b.lo;
-  return b;
-}
-
+// Store instructions per tile; fixed for a mode, so the wait counts of the
+// software pipeline do not depend on the data.
 template <int STORE>
-__device__ __forceinline__ OutRows finish_rows(const floatx16 &z, const OutBias &b, int out_dim) {
-  OutRows r;
-  r.hi = __builtin_nondeterministic_value(r.hi);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) r.lo[i] = __builtin_bit_cast(uint32_t, sigmoid(z[i], b.lo[i]));
-  if (STORE == kStoreEach && out_dim > 8) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      r.hi[i] = __builtin_bit_cast(uint32_t, sigmoid(z[4 + i], b.hi[i]));
-  }
-  return r;
-}
+constexpr int kStoresPerTile =
+    STORE == kStoreEachWide ? 16 : STORE == kStoreEach ? 8 : STORE == kStoreF16x3 ? 4 : 2;
 
 // Cache policy of the output stores: non-temporal.  The decoded rows are
 // written once and not read again by the kernel; streaming them past the L2
@@ -593,40 +592,61 @@ __device__ __forceinline__ OutRows finish_rows(const floatx16 &z, const OutBias 
 // 13 % less decode time on the 4K clustered frame than default stores).
 constexpr int kOutPolicy = 2;  // nt
 
-// Every store of the mode is always issued (rows past the width, and masked
+// Every store of a mode is always issued (rows past the width, and masked
 // lanes, get the drop offset), so the number of stores never depends on the
 // data or the width.
+// Decoded values of one lane for the store: rows r0 .. r0+3 of one query.
+// Output widths up to 8 use the rows of lane groups 0 and 1 only; the upper
+// half-wave of y[0] / y[1] takes y[2] / y[3]'s lower half first, so every lane
+// finishes 4 values of y01[0] (queries 16n, blocks 0 / 2) and 4 of y01[1]
+// (blocks 1 / 3).
+// Bit casts through by-value helpers: a __builtin_bit_cast applied directly to
+// an element of an ext_vector inside an unrolled loop is folded to element 0 by
+// this compiler.
+__device__ __forceinline__ uint32_t f32_bits(float f) { return __builtin_bit_cast(uint32_t, f); }
+__device__ __forceinline__ float bits_f32(uint32_t u) { return __builtin_bit_cast(float, u); }
+
+__device__ __forceinline__ void compact_out(floatx4 (&y)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const auto a = __builtin_amdgcn_permlane32_swap(f32_bits(y[0][r]), f32_bits(y[2][r]), false,
+                                                    false);
+    const auto b = __builtin_amdgcn_permlane32_swap(f32_bits(y[1][r]), f32_bits(y[3][r]), false,
+                                                    false);
+    y[0][r] = bits_f32(a[0]);
+    y[1][r] = bits_f32(b[0]);
+  }
+}
+
+// Store of rows r0 .. r0 + 3 of query q (of the output's first 16 rows) in the
+// given mode; rows at or past out_dim, and queries that are not ok, are
+// dropped.
 template <int STORE>
-__device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t out, int out_dim, uint32_t q,
-                                           bool ok, const OutRows &r, uint32_t out_f16) {
-  const int h = lane_id() >> 5;
-  const int r0 = 4 * h;
+__device__ __forceinline__ void store4(__amdgpu_buffer_rsrc_t out, int out_dim, uint32_t q,
+                                       bool ok, int r0, const u32x4 &v, uint32_t out_f16) {
   if constexpr (STORE == kStoreF32x4) {
     const uint32_t off = ok && r0 < out_dim ? (q * (uint32_t)out_dim + (uint32_t)r0) * 4u
                                             : kDropOffset;
-    __builtin_amdgcn_raw_buffer_store_b128(r.lo, out, off, 0, kOutPolicy);
+    __builtin_amdgcn_raw_buffer_store_b128(v, out, off, 0, kOutPolicy);
   } else if constexpr (STORE == kStoreF16x4) {
     const uint32_t off = ok && r0 < out_dim ? (q * (uint32_t)out_dim + (uint32_t)r0) * 2u
                                             : kDropOffset;
-    const float4 lo = __builtin_bit_cast(float4, r.lo);
-    const u32x2 lo16 = {pack_half2(lo.x, lo.y), pack_half2(lo.z, lo.w)};
-    __builtin_amdgcn_raw_buffer_store_b64(lo16, out, off, 0, kOutPolicy);
+    const float4 f = __builtin_bit_cast(float4, v);
+    const u32x2 h = {pack_half2(f.x, f.y), pack_half2(f.z, f.w)};
+    __builtin_amdgcn_raw_buffer_store_b64(h, out, off, 0, kOutPolicy);
   } else if constexpr (STORE == kStoreF32x3) {
-    const uint32_t off = ok && h == 0 ? q * 12u : kDropOffset;
-    const u32x3 v = {r.lo[0], r.lo[1], r.lo[2]};
-    __builtin_amdgcn_raw_buffer_store_b96(v, out, off, 0, kOutPolicy);
+    const uint32_t off = ok && r0 == 0 ? q * 12u : kDropOffset;
+    const u32x3 w = {v[0], v[1], v[2]};
+    __builtin_amdgcn_raw_buffer_store_b96(w, out, off, 0, kOutPolicy);
   } else if constexpr (STORE == kStoreF16x3) {
-    // the row's 6 bytes start at 6q: for even q the pair (0, 1) is 4-byte
-    // aligned and row 2 follows; for odd q row 0 comes first, then the
-    // aligned pair (1, 2)
-    const float4 lo = __builtin_bit_cast(float4, r.lo);
+    const float4 f = __builtin_bit_cast(float4, v);
     const bool even = (q & 1u) == 0;
     const uint32_t base = q * 6u;
-    const bool st = ok && h == 0;
+    const bool st = ok && r0 == 0;
     const uint32_t off32 = st ? (even ? base : base + 2u) : kDropOffset;
     const uint32_t off16 = st ? (even ? base + 4u : base) : kDropOffset;
-    const uint32_t pair = even ? pack_half2(lo.x, lo.y) : pack_half2(lo.y, lo.z);
-    const _Float16 single = (_Float16)(even ? lo.z : lo.x);
+    const uint32_t pair = even ? pack_half2(f.x, f.y) : pack_half2(f.y, f.z);
+    const _Float16 single = (_Float16)(even ? f.z : f.x);
     __builtin_amdgcn_raw_buffer_store_b32(pair, out, off32, 0, kOutPolicy);
     __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, single), out, off16, 0,
                                            kOutPolicy);
@@ -634,38 +654,92 @@ __device__ __forceinline__ void store_rows(__amdgpu_buffer_rsrc_t out, int out_d
     const uint32_t row = q * (uint32_t)out_dim;
     const uint32_t es = out_f16 ? 2u : 4u;
 #pragma unroll
-    for (int g = 0; g < 2; ++g) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int rr = 8 * g + 4 * h + i;
-        const uint32_t off = ok && rr < out_dim ? (row + (uint32_t)rr) * es : kDropOffset;
-        const uint32_t v = g ? r.hi[i] : r.lo[i];
-        if (out_f16) {
-          const _Float16 f = (_Float16)__builtin_bit_cast(float, v);
-          __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, f), out, off, 0,
-                                                 kOutPolicy);
-        } else {
-          __builtin_amdgcn_raw_buffer_store_b32(v, out, off, 0, kOutPolicy);
-        }
+    for (int i = 0; i < 4; ++i) {
+      const int rr = r0 + i;
+      const uint32_t off = ok && rr < out_dim ? (row + (uint32_t)rr) * es : kDropOffset;
+      if (out_f16) {
+        const _Float16 f = (_Float16)bits_f32(v[i]);
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, f), out, off, 0,
+                                               kOutPolicy);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b32(v[i], out, off, 0, kOutPolicy);
       }
     }
   }
 }
 
-// Column block 0 holds the queries of lanes 0..31, block 1 those of lanes
-// 32..63; a lane of half h stores, for each block, the query of lane
-// (block * 32 + lane % 32): its own in block h, its partner's in the other.
-// One v_permlane32_swap of (q, q) gives both: its first result holds the
-// lower half's values in both halves, its second the upper half's.
-template <int STORE>
-__device__ __forceinline__ void store_tile(__amdgpu_buffer_rsrc_t out, int out_dim, uint32_t q,
-                                           bool ok, const OutRows &b0, const OutRows &b1,
-                                           uint32_t out_f16) {
+// Finished output of a tile: sigmoid applied, with the query index and
+// validity of each stored row group.  Widths up to 8 (WIDE = false) hold two
+// 4-row groups per lane (after compact_out), wider outputs four.
+template <bool WIDE>
+struct TileOut {
+  static constexpr int G = WIDE ? 4 : 2;
+  u32x4 v[G];
+  uint32_t q[G];
+  uint32_t ok;   // bit i: group i is valid
+};
+
+// Sigmoid of the output accumulators with the scaled output biases; q and ok
+// of the lane's own query slot (lane = query slot) are redistributed to the
+// lanes that store its rows.
+template <bool WIDE>
+__device__ __forceinline__ TileOut<WIDE> finish16(floatx4 (&y)[4], const float *out_bias,
+                                                  uint32_t q, bool ok) {
+  TileOut<WIDE> o;
+  const uint32_t lane = lane_id(), g = lane >> 4;
   const uint32_t okw = ok ? 1u : 0u;
-  const auto qs = __builtin_amdgcn_permlane32_swap(q, q, false, false);
-  const auto oks = __builtin_amdgcn_permlane32_swap(okw, okw, false, false);
-  store_rows<STORE>(out, out_dim, qs[0], oks[0] != 0, b0, out_f16);
-  store_rows<STORE>(out, out_dim, qs[1], oks[1] != 0, b1, out_f16);
+  o.ok = 0;
+  if constexpr (!WIDE) {
+    compact_out(y);
+    const floatx4 b = *(const floatx4 *)(out_bias + 4 * (g & 1));
+    // lane (g, n) stores query slots (g < 2 ? n : 32 + n) and (g < 2 ? 16 + n : 48 + n)
+    const auto qs = __builtin_amdgcn_permlane16_swap(q, q, false, false);
+    const auto oks = __builtin_amdgcn_permlane16_swap(okw, okw, false, false);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o.v[i][r] = f32_bits(sigmoid(y[i][r], b[r]));
+      o.q[i] = qs[i];
+      o.ok |= (oks[i] & 1u) << i;
+    }
+  } else {
+    const floatx4 b = *(const floatx4 *)(out_bias + 4 * g);
+    // lane (g, n) stores rows 4g .. 4g+3 of query slot 16j + n of each block j:
+    // a 4x4 transpose of (row, block) of the query index and its validity
+    uint32_t tq[4] = {q, q, q, q}, tk[4] = {okw, okw, okw, okw};
+    {
+      auto a = __builtin_amdgcn_permlane32_swap(tq[0], tq[2], false, false);
+      auto b2 = __builtin_amdgcn_permlane32_swap(tq[1], tq[3], false, false);
+      tq[0] = a[0]; tq[2] = a[1]; tq[1] = b2[0]; tq[3] = b2[1];
+      a = __builtin_amdgcn_permlane16_swap(tq[0], tq[1], false, false);
+      b2 = __builtin_amdgcn_permlane16_swap(tq[2], tq[3], false, false);
+      tq[0] = a[0]; tq[1] = a[1]; tq[2] = b2[0]; tq[3] = b2[1];
+      a = __builtin_amdgcn_permlane32_swap(tk[0], tk[2], false, false);
+      b2 = __builtin_amdgcn_permlane32_swap(tk[1], tk[3], false, false);
+      tk[0] = a[0]; tk[2] = a[1]; tk[1] = b2[0]; tk[3] = b2[1];
+      a = __builtin_amdgcn_permlane16_swap(tk[0], tk[1], false, false);
+      b2 = __builtin_amdgcn_permlane16_swap(tk[2], tk[3], false, false);
+      tk[0] = a[0]; tk[1] = a[1]; tk[2] = b2[0]; tk[3] = b2[1];
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) o.v[j][r] = f32_bits(sigmoid(y[j][r], b[r]));
+      o.q[j] = tq[j];
+      o.ok |= (tk[j] & 1u) << j;
+    }
+  }
+  return o;
+}
+
+template <int STORE, bool WIDE>
+__device__ __forceinline__ void store_out16(__amdgpu_buffer_rsrc_t out, int out_dim,
+                                            const TileOut<WIDE> &o, uint32_t out_f16) {
+  const uint32_t g = lane_id() >> 4;
+  const int r0 = WIDE ? 4 * (int)g : 4 * (int)(g & 1);
+#pragma unroll
+  for (int i = 0; i < TileOut<WIDE>::G; ++i)
+    store4<STORE>(out, out_dim, o.q[i], (o.ok >> i) & 1u, r0, o.v[i], out_f16);
 }
 
 // Query data of a slot.  The loads are unconditional (a slot without a valid
@@ -755,85 +829,197 @@ __device__ __forceinline__ Group next_wgroup(const DecodeArgs &a, const Group &g
              : g;
 }
 
-// Waves per workgroup.  The staged decoder is shared by a workgroup's waves.
-// Binned kernels use 8 waves: one LDS image then serves twice as many tiles
-// (about 3 % less decode time than 4-wave workgroups on the 4K clustered frame
-// with 64-wide decoders), and a 128-wide decoder's image (about 86 KB for
-// 48-128-128-128-8) allows only one workgroup per CU anyway.  Stream kernels
-// with 64-wide decoders keep 4 waves: a workgroup restages every decoder
-// present in its group of tiles, and a group of 8 tiles holds more of them
-// (7 % more time with one decoder per texture).
-template <int HID, bool BINNED>
-constexpr int kWaves = BINNED || HID > 64 ? 8 : 4;
-template <int HID, bool BINNED>
-constexpr int kThreads = kWaves<HID, BINNED> * kWave;
-// Minimum waves per SIMD the register allocation must allow (the second
-// argument of __launch_bounds__): 4 for the 64-wide stream kernels (<= 128
-// VGPRs), 2 for the 64-wide binned kernels and 1 for 128-wide decoders.  The
-// binned instantiation of the clustered workload takes 112 VGPRs (4 waves per
-// SIMD); asking for 4 there makes the fp16-output and mip-blending
-// instantiations spill.
-template <int HID, bool BINNED>
-constexpr int kMinBlocks = HID > 64 ? 1 : 16 / kWaves<HID, BINNED>;
+// Last bin whose first slot is at or before `slot` (wave uniform, below the
+// total): 64 probes a round, one load each, so one round up to 64 decoders and
+// two up to 4096; bin_offset[0] = 0 keeps the first probe true.
+__device__ __forceinline__ uint32_t bin_of_slot(const DecodeArgs &a, uint32_t D, uint32_t slot) {
+  const uint32_t lane = lane_id();
+  uint32_t lo = 0, span = D;  // the bin lies in [lo, lo + span)
+  while (span > 1) {
+    const uint32_t step = (span + kWave - 1) / kWave;
+    const uint32_t at = lane * step;
+    const bool le = at < span && a.bin_offset[lo + (at < span ? at : 0u)] <= slot;
+    const uint32_t k = (uint32_t)__builtin_popcountll(ballot(le)) - 1;
+    lo += k * step;
+    span = min(step, span - k * step);
+  }
+  return __builtin_amdgcn_readfirstlane(lo);
+}
 
+// Waves per workgroup of every kernel of the MFMA engine, two per SIMD: a wave
+// of a 64-wide decoder holds its weights and the next tile's taps (up to 256
+// VGPRs); a 128-wide decoder's LDS image (about 86 KB for 48-128-128-128-8)
+// allows one workgroup per CU.
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWave;
+
+// Weights in registers: 64-wide hidden layers (at most 26 fragments).
+template <int HID>
+constexpr bool kRegWeights = HID == 64;
+
+// The taps of the next tile are fetched before this tile's MLP where they and
+// the weights leave the MLP its registers: up to 64 registers of taps (2 levels of
+// 16 channels) and 18 fragments.  Otherwise a tile gathers when it starts:
+// carrying 3 levels' taps (96 registers) beside the weights spilled (1080p frame of
+// 48-64-64-8: 147 us against 83 before).
+template <int NL, int CH, int PE, int HID, int NH, bool MIP>
+constexpr bool kTapsAhead =
+    kRegWeights<HID> && !MIP && NL * CH <= 32 && Net<NL, CH, PE, HID, NH>::kFrags <= 18;
+
+// Binned decode with the weights in registers.  A workgroup takes a contiguous
+// range of tiles and deals them to its waves from a counter in LDS, each wave
+// on its own: it loads a decoder when its next tile's bin differs, with no
+// barrier.  Waves w and w + 4 share a SIMD, which issues the older one first:
+// dealt evenly, waves 0-3 ended after 117 us and waves 4-7 after 170 us of the 4K
+// clustered frame; from the counter the pass (binning and decode) takes 200.0
+// instead of 205.4 us, the 1080p one 54.4 instead of 55.5.
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__((kThreads<HID, true>), (kMinBlocks<HID, true>))
-decode_binned(const DecodeArgs a) {
-  constexpr int WAVES = kWaves<HID, true>;
+__global__ void __launch_bounds__(kThreads, 2) decode_binned_reg(const DecodeArgs a) {
   using S = Shape<NL, CH, PE, HID>;
-  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+  using N = Net<NL, CH, PE, HID, NH>;
+  constexpr bool AHEAD = kTapsAhead<NL, CH, PE, HID, NH, MIP>;
+  constexpr bool WIDE = kWideRows<STORE>;
+  __shared__ __attribute__((aligned(16))) float biases[kWaves][N::kBiases];
+  const uint32_t lane = lane_id();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t nw = blockDim.x / kWave;  // waves of this workgroup, at most kWaves
   const uint32_t D = (uint32_t)a.n_decoders;
   const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
   // tiles of the permutation; never more than the buffer holds
   const uint64_t slots = min((uint64_t)bin_off(a, D), a.perm_capacity);
   const uint32_t total_tiles = (uint32_t)(slots / kWave);
-  // This workgroup's contiguous range of tiles, in workgroups numbered XCD by
-  // XCD.  Equal ranges, or with a.split (two workgroups per CU, the grid a
-  // multiple of 16) twice the tiles for the first workgroup dispatched to each
-  // CU (blockIdx < gridDim / 2): the SIMDs issue the older waves first, so two
-  // co-resident workgroups with equal work finish a third apart and the second
-  // runs its last third on half the waves.
-  uint32_t t, t_end;
-  if (a.split) {
-    const uint32_t per_xcd = gridDim.x / 8, half = per_xcd / 2;
-    const uint32_t xcd = blockIdx.x % 8, j = blockIdx.x / 8;  // j < half: first on its CU
-    const uint64_t w0 = (uint64_t)xcd * half * 3 + (j < half ? 2 * j : 2 * half + (j - half));
-    const uint64_t w1 = w0 + (j < half ? 2 : 1);
-    const uint64_t W = (uint64_t)gridDim.x / 2 * 3;
-    t = (uint32_t)(total_tiles * w0 / W);
-    t_end = (uint32_t)(total_tiles * w1 / W);
-  } else {
-    const uint32_t per = (total_tiles + gridDim.x - 1) / gridDim.x;
-    t = xcd_local_block(blockIdx.x, gridDim.x) * per;
-    t_end = min(t + per, total_tiles);
-  }
-  if (t >= t_end) return;
-  // bin holding slot 64 t: the last d with bin_offset[d] <= 64 t
-  uint32_t lo = 0, hi = D;  // invariant: bin_offset[lo] <= 64 t < bin_offset[hi]
-  while (hi - lo > 1) {
-    const uint32_t mid = (lo + hi) / 2;
-    if (bin_off(a, mid) <= t * kWave) lo = mid; else hi = mid;
-  }
-  // Tiles go in groups of consecutive tiles of one bin (weighted for 128-wide
-  // decoders), tile t + w to wave w; every wave walks the same (uniform)
-  // sequence of groups.  A wave without a tile in a group runs it with every
-  // lane masked, or, weighted, skips its MLP and stores but still takes part in
-  // its staging and prefetches.
-  constexpr bool WEIGHTED = HID > 64;
-  const uint32_t wu = __builtin_amdgcn_readfirstlane(w);
-  auto advance = [&](const Group &g) {
-    if constexpr (WEIGHTED) return next_wgroup<WAVES>(a, g, D, t_end);
-    else return next_group<WAVES>(a, g, D, t_end);
+  const uint32_t blk = xcd_local_block(blockIdx.x, gridDim.x);
+  const uint32_t t0 = (uint32_t)((uint64_t)total_tiles * blk / gridDim.x);
+  const uint32_t t_end = (uint32_t)((uint64_t)total_tiles * (blk + 1) / gridDim.x);
+  // the first four tiles of every wave are fixed (the pipeline starts with them)
+  __shared__ uint32_t dealt;
+  if (threadIdx.x == 0) dealt = 4 * nw;
+  __syncthreads();
+  if (t0 + w >= t_end) return;
+  // A tile of this wave and its bin: tiles at or past `be` belong to later bins.
+  struct Cursor {
+    uint32_t t, d, be;
   };
-  Group g0 = group_at<WAVES>(a, t, lo, bin_off(a, lo + 1) / kWave, D, t_end);
-  Group g1 = advance(g0);
-  Group g2 = advance(g1);
-  Group g3 = advance(g2);
-  // perm entry of this wave's tile in group g.  The load is unconditional (slot
+  auto seek = [&](Cursor c, uint32_t t) -> Cursor {
+    c.t = t;
+    while (t >= c.be && c.d + 1 < D) {
+      ++c.d;
+      c.be = bin_off(a, c.d + 1) / kWave;
+    }
+    return c;
+  };
+  Cursor c0;
+  c0.t = t0 + w;
+  c0.d = bin_of_slot(a, D, c0.t * kWave);
+  c0.be = bin_off(a, c0.d + 1) / kWave;
+  Cursor c1 = seek(c0, c0.t + nw), c2 = seek(c1, c1.t + nw), c3 = seek(c2, c2.t + nw);
+  // perm entry of this wave's slot in a tile.  The load is unconditional (slot
   // 0 exists whenever there is a tile) and the entry stays raw until it is
-  // used, with `has` saying whether the wave has a tile in the group: selecting
-  // right after the load would wait for it.
+  // used, with `has` saying whether the tile is in the range: selecting right
+  // after the load would wait for it.
+  struct Slot {
+    uint32_t raw;
+    bool has;
+  };
+  auto slot_query = [&](const Cursor &c) -> Slot {
+    const bool has = c.t < t_end;
+    return Slot{a.perm[has ? c.t * kWave + lane : 0u], has};
+  };
+  // Software pipeline.  Vector-memory operations complete in issue order as
+  // far as the wait counter is concerned, and stores count too, so the order
+  // in tile k is: taps of tile k+1, (after the MLP) query data of tile k+2,
+  // permutation entry of tile k+3, and only then the stores of tile k.
+  RegNet<NL, CH, PE, HID, NH> net;
+  net.lds = biases[w];
+  const Slot s0 = slot_query(c0);
+  const Slot s1 = slot_query(c1);
+  Slot p_next = slot_query(c2);  // tile 2
+  Query cur = load_query<NL, MIP>(a, s0.raw, s0.has);
+  Query q_next = load_query<NL, MIP>(a, s1.raw, s1.has);  // tile 1
+  __builtin_amdgcn_sched_barrier(0);
+  net.load(a, c0.d);
+  uint32_t held = c0.d;
+  cur = validate(a, cur);  // tile 0
+  TileTaps<NL, CH> taps;
+  if constexpr (AHEAD) fetch_taps<NL, CH>(a, cur, taps);
+  __builtin_amdgcn_sched_barrier(0);
+  // One tile: decode `cur` (taps already in flight), fetch the next tile's taps
+  // from q_in (its query data), load the next tile's decoder if it changes,
+  // prefetch query data of the tile after from p_in into q_out and the
+  // permutation entry of the tile after that into p_out, then store.
+  auto tile = [&](const Query &q_in, const Slot &p_in, Query &q_out, Slot &p_out) {
+    uint32_t next = 0;
+    if (lane == 0) next = atomicAdd(&dealt, 1u);
+    uint32_t x[S::F / 2];
+    if constexpr (AHEAD) {
+      interp_taps<NL, CH, PE>(taps, x);
+      if constexpr (PE > 0) pos_encoding<PE>(cur.u, cur.v, x + NL * CH / 2);
+    } else {
+      gather<NL, CH, PE, MIP>(a, cur, x);
+    }
+    const Query nxt = validate(a, q_in);
+    if constexpr (AHEAD) fetch_taps<NL, CH>(a, nxt, taps);
+    half8 xb[4][S::KS0];
+    to_b16<S::KS0, S::F / 2>(x, xb);
+    floatx4 y[4];
+    mlp<NL, CH, PE, HID, NH, LEAKY>(net, xb, y, a.slope_h2);
+    const TileOut<WIDE> o = finish16<WIDE>(y, net.biases() + HID * (1 + NH), cur.q, cur.valid);
+    __builtin_amdgcn_sched_barrier(0);
+    if (c1.t < t_end && c1.d != held) {
+      net.load(a, c1.d);
+      held = c1.d;
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    q_out = load_query<NL, MIP>(a, p_in.raw, p_in.has);
+    p_out = slot_query(c3);
+    __builtin_amdgcn_sched_barrier(0);
+    store_out16<STORE, WIDE>(out_rsrc, a.out_dim, o, a.out_f16);
+    cur = nxt;
+    c0 = c1;
+    c1 = c2;
+    c2 = c3;
+    c3 = seek(c3, t0 + __builtin_amdgcn_readfirstlane(next));
+  };
+  // Unrolled by two with the prefetch registers swapping roles, so a fetched
+  // value is never copied between registers (a copy would wait for the fetch).
+  Query q_b;
+  Slot p_b;
+  for (;;) {
+    tile(q_next, p_next, q_b, p_b);
+    if (c0.t >= t_end) break;
+    tile(q_b, p_b, q_next, p_next);
+    if (c0.t >= t_end) break;
+  }
+}
+
+// Binned decode with the weights in LDS (128-wide decoders): a workgroup walks
+// a contiguous range of tiles, up to eight at a time inside one bin, restaging
+// the decoder when the bin changes.
+template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
+__global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a) {
+  using S = Shape<NL, CH, PE, HID>;
+  using N = Net<NL, CH, PE, HID, NH>;
+  constexpr bool WIDE = kWideRows<STORE>;
+  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
+  const uint32_t lane = lane_id();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+  const uint32_t D = (uint32_t)a.n_decoders;
+  const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
+  const uint64_t slots = min((uint64_t)bin_off(a, D), a.perm_capacity);
+  const uint32_t total_tiles = (uint32_t)(slots / kWave);
+  const uint32_t per = (total_tiles + gridDim.x - 1) / gridDim.x;
+  const uint32_t t = xcd_local_block(blockIdx.x, gridDim.x) * per;
+  const uint32_t t_end = min(t + per, total_tiles);
+  if (t >= t_end) return;
+  const uint32_t first = bin_of_slot(a, D, t * kWave);
+  // Tiles go in weighted groups of consecutive tiles of one bin, tile t + w to
+  // wave w; every wave walks the same (uniform) sequence of groups.  A wave
+  // without a tile in a group skips its MLP and stores but still takes part in
+  // its staging and prefetches.
+  Group g0 = group_at<kWaves>(a, t, first, bin_off(a, first + 1) / kWave, D, t_end);
+  Group g1 = next_wgroup<kWaves>(a, g0, D, t_end);
+  Group g2 = next_wgroup<kWaves>(a, g1, D, t_end);
+  Group g3 = next_wgroup<kWaves>(a, g2, D, t_end);
   struct Slot {
     uint32_t raw;
     bool has;
@@ -842,17 +1028,13 @@ decode_binned(const DecodeArgs a) {
     const bool has = w < g.n;
     return Slot{a.perm[has ? (g.t + w) * kWave + lane : 0u], has};
   };
-  // Software pipeline.  Vector-memory operations complete in issue order as
-  // far as the wait counter is concerned, and stores count too, so the order
-  // at the end of tile k is: taps of tile k+1, query data of tile k+2,
-  // permutation entry of tile k+3, and only then the stores of tile k.  Tile
-  // k+1 then waits for its taps without waiting for those stores, and every
-  // prefetch has a whole tile of work to land.
   auto restage = [&](uint32_t d) {
     __syncthreads();  // every wave is done with the previous decoder
-    stage_decoder<NL, CH, PE, HID, kThreads<HID, true>>(a, d, lds);
+    stage_decoder<N, kThreads>(a, d, lds);
     __syncthreads();
   };
+  LdsNet<NL, CH, PE, HID, NH> net;
+  net.lds = lds;
   const Slot s0 = slot_query(g0);
   Query cur = validate(a, load_query<NL, MIP>(a, s0.raw, s0.has));  // tile 0
   restage(g0.d);
@@ -869,30 +1051,24 @@ decode_binned(const DecodeArgs a) {
   // order, as at its back edge, so the waits at its top need not drain.
   // Distinct offsets keep them from being merged.
 #pragma unroll
-  for (uint32_t i = 0; i < 2 * kStoresPerBlock<STORE>; ++i)
+  for (uint32_t i = 0; i < kStoresPerTile<STORE>; ++i)
     __builtin_amdgcn_raw_buffer_store_b32(0u, out_rsrc, kDropOffset + 16u * i, 0, 0);
-  // One tile: decode `cur` (taps already in flight), stage the next group's
-  // decoder if it changes, fetch the next tile's taps from q_in (its query data),
-  // prefetch query data of the tile after from p_in into q_out and the
-  // permutation entry of the tile after that into p_out, then store.
   auto tile = [&](const Query &q_in, const Slot &p_in, Query &q_out, Slot &p_out) {
-    const bool busy = !WEIGHTED || wu < g0.n;  // this wave has a tile in the group
-    OutRows r0, r1;
+    const bool busy = w < g0.n;  // this wave has a tile in the group
+    TileOut<WIDE> o;
     if (busy) {
       uint32_t x[S::F / 2];
-      if constexpr (MIP)
+      if constexpr (MIP) {
         gather<NL, CH, PE, MIP>(a, cur, x);
-      else {
+      } else {
         interp_taps<NL, CH, PE>(taps, x);
         if constexpr (PE > 0) pos_encoding<PE>(cur.u, cur.v, x + NL * CH / 2);
       }
-      half8 xb0[S::KS0], xb1[S::KS0];
-      to_b_operands<S::KS0>(x, xb0, xb1);
-      floatx16 z0, z1;
-      run_mlp<NL, CH, PE, HID, NH, LEAKY>(lds, xb0, xb1, z0, z1, a.slope_h2);
-      const OutBias ob = load_out_bias<NL, CH, PE, HID, NH, STORE>(lds, a.out_dim);
-      r0 = finish_rows<STORE>(z0, ob, a.out_dim);
-      r1 = finish_rows<STORE>(z1, ob, a.out_dim);
+      half8 xb[4][S::KS0];
+      to_b16<S::KS0, S::F / 2>(x, xb);
+      floatx4 y[4];
+      mlp<NL, CH, PE, HID, NH, LEAKY>(net, xb, y, a.slope_h2);
+      o = finish16<WIDE>(y, net.biases() + HID * (1 + NH), cur.q, cur.valid);
     }
     __builtin_amdgcn_sched_barrier(0);
     // The next group's decoder is staged here, between this tile's MLP and the
@@ -908,15 +1084,13 @@ decode_binned(const DecodeArgs a) {
     q_out = load_query<NL, MIP>(a, p_in.raw, p_in.has);
     p_out = slot_query(g3);
     __builtin_amdgcn_sched_barrier(0);
-    if (busy) store_tile<STORE>(out_rsrc, a.out_dim, cur.q, cur.valid, r0, r1, a.out_f16);
+    if (busy) store_out16<STORE, WIDE>(out_rsrc, a.out_dim, o, a.out_f16);
     cur = nxt;
     g0 = g1;
     g1 = g2;
     g2 = g3;
-    g3 = advance(g3);
+    g3 = next_wgroup<kWaves>(a, g3, D, t_end);
   };
-  // Unrolled by two with the prefetch registers swapping roles, so a fetched
-  // value is never copied between registers (a copy would wait for the fetch).
   Query q_b;
   Slot p_b;
   for (;;) {
@@ -927,243 +1101,140 @@ decode_binned(const DecodeArgs a) {
   }
 }
 
+// ---------------------------------------------------------------- stream mode
+//
+// The paper's non-shared tensor decoder (Sec. 4.4): a wave pays one full MLP
+// pass per decoder its tile holds.
+
+// Decoder of a validated query, kNoDecoder for none.  The load is unconditional
+// (validate() points an invalid query at texture 0).
+constexpr uint32_t kNoDecoder = 0xFFFFFFFFu;
+__device__ __forceinline__ uint32_t decoder_of(const DecodeArgs &a, const Query &q, uint32_t dd) {
+  return q.valid && dd < (uint32_t)a.n_decoders ? dd : kNoDecoder;
+}
+
+// Stream decode with the weights in registers (64-wide decoders).  Every wave
+// walks a contiguous run of tiles and keeps the last decoder it used: a tile
+// takes the held decoder first, then loads each other one it needs, so a run
+// over one material loads nothing.  What bounds it is the latency of those
+// loads and, on frames of one material, what bounds the binned decode.  1080p
+// frame of 16 decoders: 193 us before, when every wave read each fragment of each
+// pass through the caches.
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__((kThreads<HID, false>), (kMinBlocks<HID, false>))
-decode_stream(const DecodeArgs a) {
-  constexpr int WAVES = kWaves<HID, false>;
+__global__ void __launch_bounds__(kThreads, 2) decode_stream_reg(const DecodeArgs a) {
   using S = Shape<NL, CH, PE, HID>;
-  extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  __shared__ uint32_t next_dec[2][WAVES];
-  const uint32_t w = threadIdx.x / kWave, lane = lane_id();
+  using N = Net<NL, CH, PE, HID, NH>;
+  constexpr bool AHEAD = kTapsAhead<NL, CH, PE, HID, NH, MIP>;
+  constexpr bool WIDE = kWideRows<STORE>;
+  __shared__ __attribute__((aligned(16))) float biases[kWaves][N::kBiases];
+  const uint32_t lane = lane_id();
+  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
-  const uint32_t n_tiles = (a.n + kWave - 1) / kWave;
-  const uint32_t n_groups = (n_tiles + WAVES - 1) / WAVES;
-  const uint32_t per = (n_groups + gridDim.x - 1) / gridDim.x;
-  const uint32_t blk = xcd_local_block(blockIdx.x, gridDim.x);
-  const uint32_t g_begin = blk * per, g_end = min(g_begin + per, n_groups);
-  uint32_t staged = 0xFFFFFFFFu;
-  int parity = 0;
-  for (uint32_t g = g_begin; g < g_end; ++g) {
-    const uint32_t q = (g * WAVES + w) * kWave + lane;
-    const Query qq = validate(a, load_query<NL, MIP>(a, q, true));
-    uint32_t dq = 0xFFFFFFFFu;
-    bool live = qq.valid;
-    if (live) {
-      const uint32_t dd = a.tex_to_dec[qq.tex];
-      live = dd < (uint32_t)a.n_decoders;
-      dq = live ? dd : 0xFFFFFFFFu;
-    }
+  const uint32_t n_tiles = (uint32_t)(((uint64_t)a.n + kWave - 1) / kWave);
+  const uint32_t nw = blockDim.x / kWave;  // waves of this workgroup, at most kWaves
+  const uint64_t waves = (uint64_t)gridDim.x * nw;
+  const uint64_t me = (uint64_t)xcd_local_block(blockIdx.x, gridDim.x) * nw + w;
+  const uint32_t t_beg = (uint32_t)(n_tiles * me / waves);
+  const uint32_t t_end = (uint32_t)(n_tiles * (me + 1) / waves);
+  if (t_beg >= t_end) return;
+  auto query_of = [&](uint32_t t) { return load_query<NL, MIP>(a, t * kWave + lane, t < t_end); };
+  RegNet<NL, CH, PE, HID, NH> net;
+  net.lds = biases[w];
+  uint32_t held = kNoDecoder;
+  Query cur = query_of(t_beg);
+  Query q_next = query_of(t_beg + 1);
+  cur = validate(a, cur);
+  uint32_t dd = a.tex_to_dec[cur.tex];
+  TileTaps<NL, CH> taps;
+  if constexpr (AHEAD) fetch_taps<NL, CH>(a, cur, taps);
+  for (uint32_t t = t_beg; t < t_end; ++t) {
     uint32_t x[S::F / 2];
-    gather<NL, CH, PE, MIP>(a, qq, x);
-    half8 xb0[S::KS0], xb1[S::KS0];
-    to_b_operands<S::KS0>(x, xb0, xb1);
-    uint64_t todo = ballot(live);
-    for (;;) {
-      const uint32_t mine =
-          todo ? read_lane(dq, (uint32_t)__builtin_ctzll(todo)) : 0xFFFFFFFFu;
-      if (lane == 0) next_dec[parity][w] = mine;
-      __syncthreads();
-      uint32_t d = next_dec[parity][0];
-#pragma unroll
-      for (int k = 1; k < WAVES; ++k) d = min(d, next_dec[parity][k]);
-      parity ^= 1;
-      if (d == 0xFFFFFFFFu) break;
-      if (d != staged) {
-        stage_decoder<NL, CH, PE, HID, kThreads<HID, false>>(a, d, lds);
-        __syncthreads();
-        staged = d;
-      }
-      const bool mine_now = live && dq == d;
-      const uint64_t sel = ballot(mine_now);
-      if (sel) {
-        floatx16 z0, z1;
-        run_mlp<NL, CH, PE, HID, NH, LEAKY>(lds, xb0, xb1, z0, z1, a.slope_h2);
-        const OutBias ob = load_out_bias<NL, CH, PE, HID, NH, STORE>(lds, a.out_dim);
-        store_tile<STORE>(out_rsrc, a.out_dim, q, mine_now,
-                          finish_rows<STORE>(z0, ob, a.out_dim),
-                          finish_rows<STORE>(z1, ob, a.out_dim), a.out_f16);
-        todo &= ~sel;
-        live = live && !mine_now;
-      }
-    }
-  }
-}
-
-// ---------------------------------------------- stream mode, per-wave decoders
-//
-// The stream-mode decode for streams over several decoders.  A workgroup takes
-// groups of consecutive tiles, one per wave, as decode_stream does.  At every
-// kStreamVoteEvery-th group the waves vote: when all of them hold one and the
-// same decoder, it is staged once in LDS, and every wave reads it from there
-// until a later vote stages another.  Any other decoder a wave holds, the wave
-// evaluates on its own, one decoder after another, reading every MFMA A
-// fragment straight from that decoder's parameter block through a raw buffer
-// (rows past the output width read as zero), with no restaging and no barrier.
-// This is the paper's non-shared tensor decoder (Sec. 4.4): a wave pays one
-// full MLP pass per decoder it holds.  Used when every decoder block is 16-byte
-// aligned (the fragment loads are 16 and 8 bytes).  Restaging the union of a
-// group's decoders in LDS, the only mode of decode_stream, makes every wave
-// wait for every decoder of the group (on the 4K clustered frame, 16 decoders:
-// 1.81 ms against 0.74 ms for per-wave reads); per-wave reads alone are twice
-// as slow as one staged copy when waves share a decoder (3.2 ms against 1.6 ms
-// on an 8192^2 image).
-//
-// Fragment (layer, row block mb, K-slice s) of lane (row r = 32 mb + lane % 32,
-// half h = lane / 32): layer 0 reads the 8 features 16 s + 8 h .. + 7 of row r
-// (one 16-byte load); later layers read units 16 s + 4 h .. + 3 and
-// 16 s + 8 + 4 h .. + 3 (two 8-byte loads), the order the previous layer's
-// accumulators leave its outputs in (sigma16).
-
-__device__ __forceinline__ half8 load_frag16(__amdgpu_buffer_rsrc_t w, uint32_t off) {
-  return as_half8(__builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(w, off, 0, 0)));
-}
-
-__device__ __forceinline__ half8 load_frag8x2(__amdgpu_buffer_rsrc_t w, uint32_t off) {
-  const u32x2 lo = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(w, off, 0, 0));
-  const u32x2 hi = __builtin_bit_cast(u32x2, __builtin_amdgcn_raw_buffer_load_b64(w, off + 16u, 0, 0));
-  return as_half8(u32x4{lo[0], lo[1], hi[0], hi[1]});
-}
-
-// The decoder's biases into this wave's region of LDS (fp32, the image's bias
-// layout: the output layer's rows past its width zero and its biases scaled by
-// -log2(e)); the wave's own earlier reads of the region precede these writes.
-template <int NL, int CH, int PE, int HID>
-__device__ __forceinline__ void stage_biases_wave(const DecodeArgs &a,
-                                                  __amdgpu_buffer_rsrc_t w, float *bias) {
-  using S = Shape<NL, CH, PE, HID>;
-  const int n_layers = a.n_hidden + 2;
-  const int n_bias = HID * (1 + a.n_hidden) + 32;
-  for (int i = lane_id(); i < n_bias; i += kWave) {
-    int layer, row, dout;
-    if (i < HID * (1 + a.n_hidden)) {
-      layer = i / HID; row = i % HID; dout = HID;
+    if constexpr (AHEAD) {
+      interp_taps<NL, CH, PE>(taps, x);
+      if constexpr (PE > 0) pos_encoding<PE>(cur.u, cur.v, x + NL * CH / 2);
     } else {
-      layer = n_layers - 1; row = i - HID * (1 + a.n_hidden); dout = a.out_dim;
+      gather<NL, CH, PE, MIP>(a, cur, x);
     }
-    const size_t off =
-        layer == 0 ? 0 : (size_t)HID * (S::F + 1) + (size_t)(layer - 1) * HID * (HID + 1);
-    const int din = layer == 0 ? S::F : HID;
-    const uint32_t boff = row < dout ? (uint32_t)(off + (size_t)dout * din + row) * 2u : kPastBlock;
-    const float v = (float)__builtin_bit_cast(_Float16, __builtin_amdgcn_raw_buffer_load_b16(w, boff, 0, 0));
-    bias[i] = layer == n_layers - 1 ? v * -kLog2e : v;
-  }
-}
-
-// run_mlp with the A fragments from the decoder block `w` and the biases from
-// the wave's LDS region.
-template <int NL, int CH, int PE, int HID, int NH, bool LEAKY>
-__device__ __forceinline__ void run_mlp_direct(__amdgpu_buffer_rsrc_t w, const float *bias,
-                                               int out_dim,
-                                               const half8 (&xb0)[(NL * CH + PE) / 16],
-                                               const half8 (&xb1)[(NL * CH + PE) / 16],
-                                               floatx16 &y0, floatx16 &y1, uint32_t slope_h2) {
-  using S = Shape<NL, CH, PE, HID>;
-  const uint32_t lr = lane_id() & 31u, h = lane_id() >> 5;
-  half8 h0[S::KSH], h1[S::KSH];
-  // layer 0: F -> HID
-#pragma unroll
-  for (int mb = 0; mb < S::MB; ++mb) {
-    floatx16 c0 = bias_frag(bias, mb), c1 = c0;
-    const uint32_t base = ((mb * 32u + lr) * S::F + 8u * h) * 2u;
-#pragma unroll
-    for (int s = 0; s < S::KS0; ++s) {
-      const half8 wf = load_frag16(w, base + 32u * s);
-      c0 = mfma(wf, xb0[s], c0);
-      c1 = mfma(wf, xb1[s], c1);
-    }
-    relu_pack<LEAKY>(c0, h0[2 * mb], h0[2 * mb + 1], slope_h2);
-    relu_pack<LEAKY>(c1, h1[2 * mb], h1[2 * mb + 1], slope_h2);
-  }
-  uint32_t woff = HID * (S::F + 1);
-  const float *bl = bias + HID;
-  // hidden -> hidden
-#pragma unroll
-  for (int layer = 0; layer < NH; ++layer) {
-    half8 n0[S::KSH], n1[S::KSH];
-#pragma unroll
-    for (int mb = 0; mb < S::MB; ++mb) {
-      floatx16 c0 = bias_frag(bl, mb), c1 = c0;
-      const uint32_t base = (woff + (mb * 32u + lr) * HID + 4u * h) * 2u;
-#pragma unroll
-      for (int s = 0; s < S::KSH; ++s) {
-        const half8 wf = load_frag8x2(w, base + 32u * s);
-        c0 = mfma(wf, h0[s], c0);
-        c1 = mfma(wf, h1[s], c1);
+    const uint32_t dq = decoder_of(a, cur, dd);
+    const Query nxt = validate(a, q_next);
+    if constexpr (AHEAD) fetch_taps<NL, CH>(a, nxt, taps);
+    dd = a.tex_to_dec[nxt.tex];
+    q_next = query_of(t + 2);
+    half8 xb[4][S::KS0];
+    to_b16<S::KS0, S::F / 2>(x, xb);
+    __builtin_amdgcn_sched_barrier(0);
+    uint64_t todo = ballot(dq != kNoDecoder);
+    while (todo) {
+      uint64_t mine = ballot(dq == held) & todo;
+      if (!mine) {
+        held = read_lane(dq, (uint32_t)__builtin_ctzll(todo));
+        mine = ballot(dq == held);
+        net.load(a, held);
       }
-      relu_pack<LEAKY>(c0, n0[2 * mb], n0[2 * mb + 1], slope_h2);
-      relu_pack<LEAKY>(c1, n1[2 * mb], n1[2 * mb + 1], slope_h2);
+      floatx4 y[4];
+      mlp<NL, CH, PE, HID, NH, LEAKY>(net, xb, y, a.slope_h2);
+      const TileOut<WIDE> o =
+          finish16<WIDE>(y, net.biases() + HID * (1 + NH), cur.q, (mine >> lane) & 1);
+      store_out16<STORE, WIDE>(out_rsrc, a.out_dim, o, a.out_f16);
+      todo &= ~mine;
     }
-#pragma unroll
-    for (int s = 0; s < S::KSH; ++s) {
-      h0[s] = n0[s];
-      h1[s] = n1[s];
-    }
-    woff += HID * (HID + 1);
-    bl += HID;
+    cur = nxt;
   }
-  // output layer: rows past the width read zero; bias added by the sigmoid
-  floatx16 c0 = {}, c1 = {};
-  const uint32_t base = lr < (uint32_t)out_dim ? (woff + lr * HID + 4u * h) * 2u : kPastBlock;
-#pragma unroll
-  for (int s = 0; s < S::KSH; ++s) {
-    const half8 wf = load_frag8x2(w, base + 32u * s);
-    c0 = mfma(wf, h0[s], c0);
-    c1 = mfma(wf, h1[s], c1);
-  }
-  y0 = c0;
-  y1 = c1;
 }
 
-// groups between two votes on the staged decoder of decode_stream_mixed
+// Stream decode of 128-wide decoders.  A workgroup takes groups of eight
+// consecutive tiles, one per wave.  At every kStreamVoteEvery-th group the waves
+// vote: when all of them hold one and the same decoder, it is staged once in
+// LDS, and every wave reads it from there until a later vote stages another.
+// Any other decoder a wave holds, the wave evaluates on its own, reading every
+// MFMA A fragment straight from that decoder's parameter block, with no
+// restaging and no barrier.  Restaging the union of a group's decoders in LDS
+// would make every wave wait for every decoder of the group; per-wave reads
+// alone are twice as slow as one staged copy when waves share a decoder.
 constexpr uint32_t kStreamVoteEvery = 8;
 
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__((kThreads<HID, false>), (kMinBlocks<HID, false>))
+__global__ void __launch_bounds__(kThreads, 1)
 decode_stream_mixed(const DecodeArgs a, uint32_t image_bytes) {
-  constexpr int WAVES = kWaves<HID, false>;
-  constexpr uint32_t kNone = 0xFFFFFFFFu, kMixed = 0xFFFFFFFEu;
+  constexpr uint32_t kNone = kNoDecoder, kMixed = 0xFFFFFFFEu;
   using S = Shape<NL, CH, PE, HID>;
+  using N = Net<NL, CH, PE, HID, NH>;
+  constexpr bool WIDE = kWideRows<STORE>;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
-  __shared__ uint32_t wave_dec[2][WAVES];
+  __shared__ uint32_t wave_dec[2][kWaves];
   const uint32_t w = threadIdx.x / kWave, lane = lane_id();
-  constexpr int n_bias = HID * (1 + NH) + 32;
-  float *bias = (float *)(lds + image_bytes / 4) + (size_t)w * n_bias;  // this wave's region
   const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
-  const uint32_t n_tiles = (a.n + kWave - 1) / kWave;
-  const uint32_t n_groups = (n_tiles + WAVES - 1) / WAVES;
+  const uint32_t n_tiles = (uint32_t)(((uint64_t)a.n + kWave - 1) / kWave);
+  const uint32_t n_groups = (n_tiles + kWaves - 1) / kWaves;
   const uint32_t per = (n_groups + gridDim.x - 1) / gridDim.x;
   const uint32_t blk = xcd_local_block(blockIdx.x, gridDim.x);
   const uint32_t g_begin = blk * per, g_end = min(g_begin + per, n_groups);
-  const int block_bytes = (int)(a.dec_stride * 2);
+  LdsNet<NL, CH, PE, HID, NH> shared;
+  shared.lds = lds;
+  DirectNet<NL, CH, PE, HID, NH> own;
+  own.lds = (float *)(lds + image_bytes / 4) + (size_t)w * N::kBiases;  // this wave's region
   uint32_t staged = kNone;  // the decoder in the shared image; the same in every wave
   int parity = 0;
   for (uint32_t g = g_begin; g < g_end; ++g) {
-    const uint32_t q = (g * WAVES + w) * kWave + lane;
-    const Query qq = validate(a, load_query<NL, MIP>(a, q, true));
-    uint32_t dq = kNone;
-    bool live = qq.valid;
-    if (live) {
-      const uint32_t dd = a.tex_to_dec[qq.tex];
-      live = dd < (uint32_t)a.n_decoders;
-      dq = live ? dd : kNone;
-    }
+    const uint64_t q64 = ((uint64_t)g * kWaves + w) * kWave + lane;
+    const uint32_t q = (uint32_t)q64;
+    const Query qq = validate(a, load_query<NL, MIP>(a, q, q64 < a.n));
+    const uint32_t dq = decoder_of(a, qq, a.tex_to_dec[qq.tex]);
     uint32_t x[S::F / 2];
     gather<NL, CH, PE, MIP>(a, qq, x);
-    half8 xb0[S::KS0], xb1[S::KS0];
-    to_b_operands<S::KS0>(x, xb0, xb1);
-    uint64_t todo = ballot(live);
+    half8 xb[4][S::KS0];
+    to_b16<S::KS0, S::F / 2>(x, xb);
+    uint64_t todo = ballot(dq != kNone);
     // the wave's one decoder, kMixed for several, kNone for none
     if ((g - g_begin) % kStreamVoteEvery == 0) {
-      // the waves vote on the shared copy at every kStreamVoteEvery-th group only and
-      // run on their own in between
       const uint32_t first = todo ? read_lane(dq, (uint32_t)__builtin_ctzll(todo)) : kNone;
-      const uint32_t mine_one = ballot(live && dq != first) ? kMixed : first;
+      const uint32_t mine_one = ballot(dq != kNone && dq != first) ? kMixed : first;
       if (lane == 0) wave_dec[parity][w] = mine_one;
       __syncthreads();  // also: every wave is done with its reads of the staged image
       uint32_t common = kNone;
       bool agree = true;
 #pragma unroll
-      for (int k = 0; k < WAVES; ++k) {
+      for (int k = 0; k < kWaves; ++k) {
         const uint32_t v = wave_dec[parity][k];
         if (v == kNone) continue;
         if (v == kMixed || (common != kNone && v != common)) agree = false;
@@ -1172,32 +1243,26 @@ decode_stream_mixed(const DecodeArgs a, uint32_t image_bytes) {
       parity ^= 1;
       if (agree && common != kNone && common != staged) {
         // every wave of the group holds this one decoder: share one staged copy
-        stage_decoder<NL, CH, PE, HID, kThreads<HID, false>>(a, common, lds);
+        stage_decoder<N, kThreads>(a, common, lds);
         __syncthreads();
         staged = common;
       }
     }
     while (todo) {
       const uint32_t d = read_lane(dq, (uint32_t)__builtin_ctzll(todo));
-      const bool mine = live && dq == d;
-      floatx16 z0, z1;
-      OutBias ob;
+      const bool mine = dq == d;
+      floatx4 y[4];
+      const float *ob;
       if (d == staged) {
-        run_mlp<NL, CH, PE, HID, NH, LEAKY>(lds, xb0, xb1, z0, z1, a.slope_h2);
-        ob = load_out_bias<NL, CH, PE, HID, NH, STORE>(lds, a.out_dim);
+        mlp<NL, CH, PE, HID, NH, LEAKY>(shared, xb, y, a.slope_h2);
+        ob = shared.biases();
       } else {
-        const __amdgpu_buffer_rsrc_t wrs = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(a.params + (size_t)d * (size_t)a.dec_stride), 0, block_bytes, 0x00020000);
-        stage_biases_wave<NL, CH, PE, HID>(a, wrs, bias);
-        run_mlp_direct<NL, CH, PE, HID, NH, LEAKY>(wrs, bias, a.out_dim, xb0, xb1, z0, z1,
-                                                   a.slope_h2);
-        const float *bo = bias + HID * (1 + NH);  // the output layer's scaled biases
-        ob.lo = *(const floatx4 *)(bo + 4 * (lane >> 5));
-        ob.hi = STORE == kStoreEach && a.out_dim > 8 ? *(const floatx4 *)(bo + 8 + 4 * (lane >> 5))
-                                                     : ob.lo;
+        own.open(a, d);
+        mlp<NL, CH, PE, HID, NH, LEAKY>(own, xb, y, a.slope_h2);
+        ob = own.biases();
       }
-      store_tile<STORE>(out_rsrc, a.out_dim, q, mine, finish_rows<STORE>(z0, ob, a.out_dim),
-                        finish_rows<STORE>(z1, ob, a.out_dim), a.out_f16);
+      const TileOut<WIDE> o = finish16<WIDE>(y, ob + HID * (1 + NH), q, mine);
+      store_out16<STORE, WIDE>(out_rsrc, a.out_dim, o, a.out_f16);
       todo &= ~ballot(mine);
     }
   }

@@ -8,74 +8,68 @@
 namespace ntc {
 namespace {
 
-template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-int launch_shape(const DecodeArgs &a, hipStream_t stream) {
-  const Image im = image_of<NL, CH, PE, HID>(NH);
-  const size_t lds = (size_t)im.bytes;
-  int dev = 0, cus = 256;
+// Workgroups of `fn` that fill the current device at once (one round, no tail
+// of late workgroups).
+inline uint64_t resident_groups(const void *fn, int threads, size_t lds) {
+  int dev = 0, cus = 256, per_cu = 0;
   if (hipGetDevice(&dev) == hipSuccess)
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (!a.bin_offset && a.n_decoders > 1 && a.dec_stride % 8 == 0 &&
-      ((uintptr_t)a.params & 15) == 0) {
-    // stream mode over several decoders, every block 16-byte aligned: a shared staged
-    // decoder where a whole group agrees on one, per-wave fragment reads elsewhere
-    constexpr int waves = kWaves<HID, false>, threads = waves * kWave;
-    const uint32_t image_bytes = ((uint32_t)im.bytes + 15u) & ~15u;
-    const size_t mlds = image_bytes + (size_t)waves * (HID * (1 + NH) + 32) * sizeof(float);
-    const void *fm = (const void *)decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
-    if (mlds > 64 * 1024 &&
-        hipFuncSetAttribute(fm, hipFuncAttributeMaxDynamicSharedMemorySize, (int)mlds) != hipSuccess)
-      return NTC_ERR_HIP;
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fm, threads, mlds) != hipSuccess ||
-        per_cu < 1)
-      per_cu = 1;
-    const uint64_t tiles = ((uint64_t)a.n + kWave - 1) / kWave;
-    uint64_t blocks = (tiles + waves - 1) / waves;
-    if (blocks > (uint64_t)cus * per_cu) blocks = (uint64_t)cus * per_cu;
-    if (blocks == 0) return NTC_OK;
-    hipLaunchKernelGGL((decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
-                       dim3((unsigned)blocks), dim3(threads), mlds, stream, a, image_bytes);
-    return hip_status(hipGetLastError());
-  }
-  if (a.gather == NTC_GATHER_STAGED) {
-    // the LDS-staged gather: binned, no mip blending, 2 levels, widths up to 8
-    // (checked by the caller)
-    if constexpr (!MIP && NL == 2)
-      if (a.bin_offset && a.out_dim <= 8) return launch_binned16<NL, CH, PE, HID, NH, STORE, LEAKY>(a, stream);
-    return NTC_ERR_UNSUPPORTED;
-  }
-  const void *fn = a.bin_offset ? (const void *)decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>
-                                : (const void *)decode_stream<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
-  if (lds > 64 * 1024) {
-    if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) !=
-        hipSuccess)
-      return NTC_ERR_HIP;
-  }
-  // every workgroup resident at once: one round, no tail of late workgroups
-  int per_cu = 0;
-  const bool binned = a.bin_offset != nullptr;
-  const int waves = binned ? kWaves<HID, true> : kWaves<HID, false>;
-  const int threads = waves * kWave;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
-  const uint64_t cap = (uint64_t)cus * (uint64_t)per_cu;
+  return (uint64_t)cus * (uint64_t)per_cu;
+}
+
+template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
+int launch_shape(const DecodeArgs &a, hipStream_t stream) {
+  using N = Net<NL, CH, PE, HID, NH>;
+  if (a.gather == NTC_GATHER_STAGED) {
+    // the LDS-staged gather: binned, no mip blending, 2 levels, widths up to 8
+    // (checked by the caller)
+    if constexpr (!MIP && NL == 2 && !kWideRows<STORE>)
+      if (a.bin_offset && a.out_dim <= 8) return launch_binned16<NL, CH, PE, HID, NH, STORE, LEAKY>(a, stream);
+    return NTC_ERR_UNSUPPORTED;
+  }
   const uint64_t tiles = a.bin_offset ? (uint64_t)a.max_tiles : ((uint64_t)a.n + kWave - 1) / kWave;
-  uint64_t blocks = (tiles + waves - 1) / waves;
-  if (blocks > cap) blocks = cap;
+  uint64_t blocks = (tiles + kWaves - 1) / kWaves;
   if (blocks == 0) return NTC_OK;
-  if (a.bin_offset) {
-    // two workgroups on every CU: the first dispatched to a CU takes two
-    // thirds of the CU's tiles (measured 3-4 % less time on the 4K clustered
-    // frame than equal ranges; 3:1 is slower again)
-    DecodeArgs b = a;
-    b.split = per_cu == 2 && blocks == cap && blocks % 16 == 0 ? 1u : 0u;
-    hipLaunchKernelGGL((decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), dim3((unsigned)blocks),
-                       dim3(threads), lds, stream, b);
-  } else
-    hipLaunchKernelGGL((decode_stream<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), dim3((unsigned)blocks),
-                       dim3(threads), lds, stream, a);
+  if constexpr (kRegWeights<HID>) {
+    const void *fn = a.bin_offset
+                         ? (const void *)decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>
+                         : (const void *)decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
+    const uint64_t cap = resident_groups(fn, kThreads, 0);  // workgroups of kWaves waves
+    // Waves share nothing but the deal of tiles, so a call that does not fill the
+    // chip takes narrower workgroups and reaches every CU (65,536 queries: 129
+    // workgroups of 8 waves sit on half of the 256 CUs).
+    uint64_t waves = kWaves;
+    while (waves > 1 && tiles <= cap * waves / 2) waves /= 2;
+    blocks = (tiles + waves - 1) / waves;
+    if (blocks > cap * (kWaves / waves)) blocks = cap * (kWaves / waves);
+    const dim3 grid((unsigned)blocks), threads((unsigned)waves * kWave);
+    if (a.bin_offset)
+      hipLaunchKernelGGL((decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
+                         0, stream, a);
+    else
+      hipLaunchKernelGGL((decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
+                         0, stream, a);
+  } else {
+    const uint32_t image_bytes = ((uint32_t)N::kImageBytes + 15u) & ~15u;
+    const void *fn = a.bin_offset
+                         ? (const void *)decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>
+                         : (const void *)decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
+    const size_t lds = image_bytes + (a.bin_offset ? 0 : kWaves * N::kBiases * sizeof(float));
+    if (lds > 64 * 1024 &&
+        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return NTC_ERR_HIP;
+    const uint64_t cap = resident_groups(fn, kThreads, lds);
+    if (blocks > cap) blocks = cap;
+    if (a.bin_offset)
+      hipLaunchKernelGGL((decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
+                         dim3((unsigned)blocks), dim3(kThreads), lds, stream, a);
+    else
+      hipLaunchKernelGGL((decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
+                         dim3((unsigned)blocks), dim3(kThreads), lds, stream, a, image_bytes);
+  }
   return hip_status(hipGetLastError());
 }
 
@@ -85,7 +79,8 @@ int launch_store(const DecodeArgs &a, hipStream_t stream) {
     return a.out_f16 ? launch_shape<NL, CH, PE, HID, NH, MIP, kStoreF16x3, LEAKY>(a, stream)
                      : launch_shape<NL, CH, PE, HID, NH, MIP, kStoreF32x3, LEAKY>(a, stream);
   if (a.out_dim != 4 && a.out_dim != 8)
-    return launch_shape<NL, CH, PE, HID, NH, MIP, kStoreEach, LEAKY>(a, stream);
+    return a.out_dim > 8 ? launch_shape<NL, CH, PE, HID, NH, MIP, kStoreEachWide, LEAKY>(a, stream)
+                         : launch_shape<NL, CH, PE, HID, NH, MIP, kStoreEach, LEAKY>(a, stream);
   return a.out_f16 ? launch_shape<NL, CH, PE, HID, NH, MIP, kStoreF16x4, LEAKY>(a, stream)
                    : launch_shape<NL, CH, PE, HID, NH, MIP, kStoreF32x4, LEAKY>(a, stream);
 }
