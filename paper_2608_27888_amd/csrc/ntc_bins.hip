@@ -26,9 +26,9 @@
 // scan (workgroup d) turns row d of hist into its exclusive prefix over slices
 // and writes bin_count[d]; place scans bin_count into the padded offsets and
 // starts its cursors at bin_offset[d] + hist[d][g].
-// Inside a 64-query row the lanes that share a decoder id are ranked with a
-// ballot and a lane count, one pass per distinct id of the row, so the order
-// inside a bin is ascending query index and the permutation is unique.  With at
+// Inside a 64-query row the lanes that share a decoder id are ranked with
+// ballots and lane counts (peel_row, match_row), so the order inside a bin is
+// ascending query index and the permutation is unique.  With at
 // most 64 decoders the wave's counters (count) and cursors (place) live in one
 // register, lane k holding decoder k's, and a row costs no LDS access; with more
 // they live in a wave-private LDS table.  A wave issues the id loads of a whole
@@ -111,59 +111,147 @@ __device__ __forceinline__ void load_batch(const uint32_t *__restrict__ tex_id,
   }
 }
 
-// Table of one value per decoder: lane k of a register (REG) or word k of a
-// wave-private LDS array.
-template <bool REG>
-struct WaveTable {
-  uint32_t reg;
-  uint32_t *lds;
-  // value of decoder dl (wave uniform)
-  __device__ __forceinline__ uint32_t get(uint32_t dl) const {
-    if constexpr (REG) return __builtin_amdgcn_readlane(reg, dl);
-    else return lds[dl];
+// A row of 64 queries is ranked by decoder in one of two ways, with the same
+// result; the wave's table of one value per decoder (REG: lane k of `reg`, else
+// word k of the wave's LDS table) advances by the row's counts.
+//   peel : one pass per distinct decoder of the row (a ballot and a lane read),
+//          15 instructions each, half of them on the CU's one scalar unit.
+//   match: every lane finds the lanes with its decoder from ballots of the id's
+//          B bits: 4 vector instructions a bit whatever the row holds, no scalar
+//          chain.
+// Rows of large screen regions hold one or two decoders, where peeling is faster
+// (4K clustered frame, 16 decoders, 1.98 a row: 34.5 us against 41 for matching
+// every row); rows of small tiles hold many (1080p, 64 decoders in 8x8 tiles, 7.6 a
+// row: 30.2 us peeling, 19.8 matching).  So with more than 16 decoders the first
+// row of a batch of 16 is peeled, and when it held more than kPeelMost decoders
+// the other rows are matched.  With at most 4 decoders (2 bits) every row is
+// matched (65,536 queries of 2 decoders: 13.1 -> 12.1 us); with 5 to 16 every row is
+// peeled (the choice alone cost the 4K clustered frame 2 us).
+constexpr uint32_t kPeelMost = 4;
+
+// Lanes of `valid` whose value equals v, compared in its low B bits; v may differ
+// per lane.  bal: ballots of those bits.
+template <int B>
+struct RowBits {
+  uint64_t valid, bal[B > 0 ? B : 1];
+  __device__ __forceinline__ RowBits(uint32_t d, uint64_t valid_lanes) : valid(valid_lanes) {
+#pragma unroll
+    for (int b = 0; b < B; ++b) bal[b] = ballot((d >> b) & 1u);
   }
-  // adds c to decoder dl's value (called by every lane; `leader` is one lane):
-  // a no-return LDS atomic does not wait for the old value
-  __device__ __forceinline__ void add(uint32_t dl, uint32_t c, uint32_t lane, bool leader) {
-    if constexpr (REG) reg += lane == dl ? c : 0u;
-    else if (leader) atomicAdd(&lds[dl], c);
+  __device__ __forceinline__ uint64_t equal(uint32_t v) const {
+    uint32_t lo = (uint32_t)valid, hi = (uint32_t)(valid >> 32);
+#pragma unroll
+    for (int b = 0; b < B; ++b) {
+      const uint32_t m = (uint32_t)__builtin_amdgcn_sbfe((int)v, b, 1);  // all ones or zero
+      lo &= ~((uint32_t)bal[b] ^ m);
+      hi &= ~((uint32_t)(bal[b] >> 32) ^ m);
+    }
+    return (uint64_t)hi << 32 | lo;
   }
 };
 
-// Ranks the valid lanes of one row (d != kOutside) by decoder: each lane gets
-// the table value of its decoder plus the number of lanes below it with the same
-// decoder, and the table advances by the row's count of each decoder.
+__device__ __forceinline__ uint32_t popcount64(uint64_t m) {
+  return (uint32_t)__builtin_popcountll(m);
+}
+
+// Number of decoder-id bits the row functions are compiled for: the next of
+// these that holds D ids, or with LDS tables D + 1 (id D counts the invalid).
+constexpr int id_bits(uint32_t D) {
+  return D <= 1 ? 0 : D <= 4 ? 2 : D <= 16 ? 4 : D <= 64 ? 6 : D < 256 ? 8 : D < 1024 ? 10 : 13;
+}
+constexpr bool peels(int bits) { return bits > 2; }
+constexpr bool matches(int bits) { return bits <= 2 || bits > 4; }
+
+// d: decoder ids, kOutside for a lane that does not count.  RANK: returns each
+// lane's slot, its decoder's value plus the number of lanes below it with the
+// same decoder.  (The LDS operations of a wave execute in order, so rows take
+// their values in order.)
 template <bool REG, bool RANK>
-__device__ __forceinline__ uint32_t rank_row(uint32_t d, WaveTable<REG> &t, uint32_t lane) {
+__device__ __forceinline__ uint32_t peel_row(uint32_t d, uint32_t &reg, uint32_t *table,
+                                             uint32_t lane, uint32_t &distinct) {
   uint64_t todo = ballot(d != kOutside);
   uint32_t pos = 0;
+  distinct = 0;
   while (todo) {
     const uint32_t leader = (uint32_t)__builtin_ctzll(todo);
     const uint32_t dl = read_lane(d, leader);
     const uint64_t same = ballot(d == dl) & todo;
-    const uint32_t c = (uint32_t)__builtin_popcountll(same);
-    if constexpr (RANK && !REG) {
-      // LDS table: the leader's returning atomic reads and advances the cursor
-      uint32_t old = 0;
-      if (lane == leader) old = atomicAdd(&t.lds[dl], c);
-      pos = d == dl ? read_lane(old, leader) + lanes_below(same) : pos;
-    } else {
+    const uint32_t c = popcount64(same);
+    if constexpr (REG) {
       if constexpr (RANK) {
-        const uint32_t at = t.get(dl);
+        const uint32_t at = read_lane(reg, dl);
         pos = d == dl ? at + lanes_below(same) : pos;
       }
-      t.add(dl, c, lane, lane == leader);
+      reg += lane == dl ? c : 0u;
+    } else if constexpr (RANK) {  // the leader's returning atomic reads and advances
+      uint32_t old = 0;
+      if (lane == leader) old = atomicAdd(&table[dl], c);
+      pos = d == dl ? read_lane(old, leader) + lanes_below(same) : pos;
+    } else if (lane == leader) {
+      atomicAdd(&table[dl], c);
     }
     todo &= ~same;
+    ++distinct;
   }
   return pos;
+}
+
+template <bool REG, bool RANK, int B>
+__device__ __forceinline__ uint32_t match_row(uint32_t d, uint32_t &reg, uint32_t *table,
+                                              uint32_t lane) {
+  const RowBits<B> row(d, ballot(d != kOutside));
+  if constexpr (REG && !RANK) {
+    reg += popcount64(row.equal(lane));
+    return 0;
+  } else {
+    const uint64_t same = row.equal(d);
+    const uint32_t rank = lanes_below(same);
+    uint32_t at = 0;
+    if constexpr (REG) {
+      at = B == 0 ? read_lane(reg, 0)
+                  : (uint32_t)__builtin_amdgcn_ds_bpermute((int)(d << 2), (int)reg);
+      reg += popcount64(row.equal(lane));
+    } else {
+      uint32_t old = 0;  // the first lane of each decoder reads and advances its value
+      if (d != kOutside && rank == 0) old = atomicAdd(&table[d], popcount64(same));
+      if constexpr (RANK) {
+        const uint32_t lo = (uint32_t)same, hi = (uint32_t)(same >> 32) | 1u << 31;
+        const uint32_t first =
+            lo ? (uint32_t)__builtin_ctz(lo) : 32u + (uint32_t)__builtin_ctz(hi);
+        at = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(first << 2), (int)old);
+      }
+    }
+    return at + rank;
+  }
+}
+
+// The rows of a batch, peeled or matched; emit(j, slot) for every row j (RANK).
+template <bool REG, bool RANK, int B, typename Emit>
+__device__ __forceinline__ void batch_rows(const uint32_t (&d)[kBatchRows], uint32_t &reg,
+                                           uint32_t *table, uint32_t lane, Emit emit) {
+  constexpr int kFirst = peels(B) && matches(B) ? 1 : 0;
+  uint32_t distinct = kPeelMost + 1, unused;
+  if constexpr (kFirst) emit(0, peel_row<REG, RANK>(d[0], reg, table, lane, distinct));
+  if constexpr (matches(B)) {
+    if (distinct > kPeelMost) {
+#pragma unroll
+      for (int j = kFirst; j < kBatchRows; ++j)
+        emit(j, match_row<REG, RANK, B>(d[j], reg, table, lane));
+      return;
+    }
+  }
+  if constexpr (peels(B)) {
+#pragma unroll
+    for (int j = kFirst; j < kBatchRows; ++j)
+      emit(j, peel_row<REG, RANK>(d[j], reg, table, lane, unused));
+  }
 }
 
 // REG: register tables (n_decoders <= 64).  tot (REG only): the workgroup's
 // sums over its waves, column b of tot[n_decoders + 1][gridDim.x], with hist
 // holding each wave's exclusive prefix over the workgroup's waves; NULL: hist
 // holds each wave's own counts.
-template <bool REG, int WAVES>
+template <bool REG, int WAVES, int B>
 __global__ void __launch_bounds__(WAVES * kWave)
 bins_count(const uint32_t *__restrict__ tex_id, uint32_t n,
            const uint32_t *__restrict__ tex_to_dec, uint32_t n_textures, uint32_t n_decoders,
@@ -174,33 +262,32 @@ bins_count(const uint32_t *__restrict__ tex_id, uint32_t n,
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const uint32_t cols = n_decoders + 1, n_slices = gridDim.x * WAVES;
   const Slice sl = slice_of<WAVES>(b, w, chunk, n);
-  WaveTable<REG> h{0u, lds + w * cols};
+  uint32_t counts = 0, *table = lds + w * cols;
   if constexpr (!REG)
-    for (uint32_t i = lane; i < cols; i += kWave) h.lds[i] = 0;
+    for (uint32_t i = lane; i < cols; i += kWave) table[i] = 0;
   // With the register table the invalid queries are counted apart, in a
   // wave-uniform counter, so that all 64 lanes can hold decoders.
   uint32_t invalid = 0;
   for (uint64_t base = sl.beg; base < sl.end; base += kWaveQuantum) {
     uint32_t d[kBatchRows];
     load_batch(tex_id, tex_to_dec, n_textures, n_decoders, n_decoders, base, sl.end, lane, d);
+    if constexpr (REG) {
 #pragma unroll
-    for (int j = 0; j < kBatchRows; ++j) {
-      if constexpr (REG) {
-        const uint64_t bad = ballot(d[j] == n_decoders);
-        invalid += (uint32_t)__builtin_popcountll(bad);
-        rank_row<REG, false>(d[j] == n_decoders ? kOutside : d[j], h, lane);
-      } else {
-        rank_row<REG, false>(d[j], h, lane);
+      for (int j = 0; j < kBatchRows; ++j) {
+        const bool bad = d[j] == n_decoders;
+        invalid += popcount64(ballot(bad));
+        d[j] = bad ? kOutside : d[j];
       }
     }
+    batch_rows<REG, false, B>(d, counts, table, lane, [](int, uint32_t) {});
   }
   if constexpr (REG) {
     const size_t col = b * WAVES + w;
     if (!tot) {
-      if (lane < n_decoders) hist[(size_t)lane * n_slices + col] = h.reg;
+      if (lane < n_decoders) hist[(size_t)lane * n_slices + col] = counts;
       if (lane == 0) hist[(size_t)n_decoders * n_slices + col] = invalid;
     } else {
-      part[w][lane] = h.reg;
+      part[w][lane] = counts;
       if (lane == 0) part[w][kWave] = invalid;
       __syncthreads();
       if (lane < n_decoders) {
@@ -288,7 +375,7 @@ bins_scan(uint32_t *__restrict__ hist, uint32_t n_slices, uint32_t n_decoders,
 }
 
 // Place of the three-kernel path.
-template <bool REG>
+template <bool REG, int B>
 __global__ void __launch_bounds__(kBlock)
 bins_place(const uint32_t *__restrict__ tex_id, uint32_t n,
            const uint32_t *__restrict__ tex_to_dec, uint32_t n_textures, uint32_t n_decoders,
@@ -334,16 +421,14 @@ bins_place(const uint32_t *__restrict__ tex_id, uint32_t n,
   }
   if (b == 0 && threadIdx.x == 0) bin_offset[D] = total;
   __syncthreads();
-  WaveTable<REG> cur{0u, lds + w * D};
-  if constexpr (REG) cur.reg = lane < D ? cur.lds[lane] : 0u;
+  uint32_t *table = lds + w * D;
+  uint32_t cursors = REG && lane < D ? table[lane] : 0u;
   for (uint64_t base = sl.beg; base < sl.end; base += kWaveQuantum) {
     if (base != sl.beg)
       load_batch(tex_id, tex_to_dec, n_textures, D, kOutside, base, sl.end, lane, d);
-#pragma unroll
-    for (int j = 0; j < kBatchRows; ++j) {
-      const uint32_t pos = rank_row<REG, true>(d[j], cur, lane);
+    batch_rows<REG, true, B>(d, cursors, table, lane, [&](int j, uint32_t pos) {
       if (d[j] != kOutside) perm[pos] = (uint32_t)(base + (uint64_t)j * kWave + lane);
-    }
+    });
   }
 }
 
@@ -351,7 +436,7 @@ bins_place(const uint32_t *__restrict__ tex_id, uint32_t n,
 // come from tot and from this workgroup's columns of hist.
 // Eight waves per SIMD (with 16-wave workgroups two per CU), so every
 // workgroup of a 4K frame is resident at once (the scalar registers decide).
-template <int WAVES>
+template <int WAVES, int B>
 __global__ void __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(8)))
 bins_place_sum(const uint32_t *__restrict__ tex_id, uint32_t n,
                const uint32_t *__restrict__ tex_to_dec, uint32_t n_textures,
@@ -429,31 +514,42 @@ bins_place_sum(const uint32_t *__restrict__ tex_id, uint32_t n,
   __syncthreads();
   // this wave's cursor of decoder k (lane k): the bin's offset, the queries of
   // the workgroups before this one, then those of this workgroup's earlier waves
-  WaveTable<true> cur{0u, nullptr};
-  if (lane < D) cur.reg = start[lane] + before[lane] + hist[(size_t)lane * n_slices + b * WAVES + w];
+  uint32_t cursors = 0;
+  if (lane < D) cursors = start[lane] + before[lane] + hist[(size_t)lane * n_slices + b * WAVES + w];
   for (uint64_t base = sl.beg; base < sl.end; base += kWaveQuantum) {
     if (base != sl.beg)
       load_batch(tex_id, tex_to_dec, n_textures, D, kOutside, base, sl.end, lane, d);
-#pragma unroll
-    for (int j = 0; j < kBatchRows; ++j) {
-      const uint32_t pos = rank_row<true, true>(d[j], cur, lane);
+    batch_rows<true, true, B>(d, cursors, nullptr, lane, [&](int j, uint32_t pos) {
       if (d[j] != kOutside) perm[pos] = (uint32_t)(base + (uint64_t)j * kWave + lane);
-    }
+    });
   }
 }
 
+// Arguments of one binning.
+struct BinsCall {
+  const uint32_t *tex_id, *tex_to_dec;
+  uint32_t n, n_textures, D, align, chunk;
+  uint32_t *hist, *tot, *bin_count, *bin_offset, *perm, *status, *invalid_out;
+  dim3 grid;
+  hipStream_t stream;
+};
+
 // The two kernels of the register-table path, on workgroups of WAVES waves.
-template <int WAVES>
-void launch_sum(const uint32_t *tex_id, int64_t n, const uint32_t *tex_to_dec,
-                int32_t n_textures, uint32_t D, int32_t align, const BinsLayout &L,
-                uint32_t *hist, uint32_t *tot, uint32_t *bin_count, uint32_t *bin_offset,
-                uint32_t *perm, uint32_t *status, uint32_t *invalid_out, hipStream_t stream) {
-  const dim3 grid((unsigned)L.blocks), block(WAVES * kWave);
-  hipLaunchKernelGGL((bins_count<true, WAVES>), grid, block, 0, stream, tex_id, (uint32_t)n,
-                     tex_to_dec, (uint32_t)n_textures, D, (uint32_t)L.chunk, hist, tot);
-  hipLaunchKernelGGL(bins_place_sum<WAVES>, grid, block, 0, stream, tex_id, (uint32_t)n,
-                     tex_to_dec, (uint32_t)n_textures, D, (uint32_t)align, (uint32_t)L.chunk,
-                     hist, tot, bin_count, bin_offset, perm, status, invalid_out);
+template <int WAVES, int B>
+void launch_sum(const BinsCall &c) {
+  const dim3 block(WAVES * kWave);
+  hipLaunchKernelGGL((bins_count<true, WAVES, B>), c.grid, block, 0, c.stream, c.tex_id, c.n,
+                     c.tex_to_dec, c.n_textures, c.D, c.chunk, c.hist, c.tot);
+  hipLaunchKernelGGL((bins_place_sum<WAVES, B>), c.grid, block, 0, c.stream, c.tex_id, c.n,
+                     c.tex_to_dec, c.n_textures, c.D, c.align, c.chunk, c.hist, c.tot, c.bin_count,
+                     c.bin_offset, c.perm, c.status, c.invalid_out);
+}
+
+template <int B>
+void launch_sum_waves(const BinsCall &c, int waves) {
+  if (waves == 16) launch_sum<16, B>(c);
+  else if (waves == 8) launch_sum<8, B>(c);
+  else launch_sum<4, B>(c);
 }
 
 // Lets a kernel use more than the default 64 KB of dynamic LDS.
@@ -463,6 +559,25 @@ int allow_lds(const void *kernel, size_t bytes) {
                  hipSuccess
              ? NTC_OK
              : NTC_ERR_HIP;
+}
+
+// The three kernels.
+template <bool REG, int B>
+int launch_three(const BinsCall &c) {
+  const size_t lds_count = REG ? 0 : (size_t)kWavesPerBlock * (c.D + 1) * sizeof(uint32_t);
+  const size_t lds_place = (size_t)kWavesPerBlock * c.D * sizeof(uint32_t);
+  int st = allow_lds((const void *)bins_count<REG, kWavesPerBlock, B>, lds_count);
+  if (st == NTC_OK) st = allow_lds((const void *)bins_place<REG, B>, lds_place);
+  if (st != NTC_OK) return st;
+  const dim3 block(kBlock);
+  hipLaunchKernelGGL((bins_count<REG, kWavesPerBlock, B>), c.grid, block, lds_count, c.stream,
+                     c.tex_id, c.n, c.tex_to_dec, c.n_textures, c.D, c.chunk, c.hist, nullptr);
+  hipLaunchKernelGGL(bins_scan, dim3(c.D + 1), dim3(kScanThreads), 0, c.stream, c.hist,
+                     c.grid.x * kWavesPerBlock, c.D, c.bin_count, c.status, c.invalid_out);
+  hipLaunchKernelGGL((bins_place<REG, B>), c.grid, block, lds_place, c.stream, c.tex_id, c.n,
+                     c.tex_to_dec, c.n_textures, c.D, c.align, c.chunk, c.hist, c.bin_count,
+                     c.bin_offset, c.perm);
+  return NTC_OK;
 }
 
 }  // namespace
@@ -510,48 +625,20 @@ int launch_build_bins(const uint32_t *tex_id, int64_t n, const uint32_t *tex_to_
   uint32_t *status = (uint32_t *)workspace;
   uint32_t *hist = status + kStatusWords;
   const uint32_t D = (uint32_t)n_decoders;
-  if (L.sum) {
-    uint32_t *tot = hist + L.hist_words;
-    if (L.waves == 16)
-      launch_sum<16>(tex_id, n, tex_to_dec, n_textures, D, align, L, hist, tot, bin_count,
-                     bin_offset, perm, status, invalid_out, stream);
-    else if (L.waves == 8)
-      launch_sum<8>(tex_id, n, tex_to_dec, n_textures, D, align, L, hist, tot, bin_count,
-                    bin_offset, perm, status, invalid_out, stream);
-    else
-      launch_sum<4>(tex_id, n, tex_to_dec, n_textures, D, align, L, hist, tot, bin_count,
-                    bin_offset, perm, status, invalid_out, stream);
-    return hip_status(hipGetLastError());
+  const BinsCall c = {tex_id, tex_to_dec, (uint32_t)n, (uint32_t)n_textures, D, (uint32_t)align,
+                      (uint32_t)L.chunk, hist, hist + L.hist_words, bin_count, bin_offset, perm,
+                      status, invalid_out, dim3((unsigned)L.blocks), stream};
+  int st = NTC_OK;
+  switch (id_bits(D)) {
+    case 0: L.sum ? launch_sum_waves<0>(c, L.waves) : (void)(st = launch_three<true, 0>(c)); break;
+    case 2: L.sum ? launch_sum_waves<2>(c, L.waves) : (void)(st = launch_three<true, 2>(c)); break;
+    case 4: L.sum ? launch_sum_waves<4>(c, L.waves) : (void)(st = launch_three<true, 4>(c)); break;
+    case 6: L.sum ? launch_sum_waves<6>(c, L.waves) : (void)(st = launch_three<true, 6>(c)); break;
+    case 8: st = launch_three<false, 8>(c); break;
+    case 10: st = launch_three<false, 10>(c); break;
+    default: st = launch_three<false, 13>(c); break;
   }
-  const uint32_t n_slices = (uint32_t)L.blocks * kWavesPerBlock;
-  const size_t lds_count = L.reg ? 0 : (size_t)kWavesPerBlock * (D + 1) * sizeof(uint32_t);
-  const size_t lds_place = (size_t)kWavesPerBlock * D * sizeof(uint32_t);
-  const void *count_fn = L.reg ? (const void *)bins_count<true, kWavesPerBlock>
-                               : (const void *)bins_count<false, kWavesPerBlock>;
-  const void *place_fn = L.reg ? (const void *)bins_place<true> : (const void *)bins_place<false>;
-  int st = allow_lds(count_fn, lds_count);
-  if (st == NTC_OK) st = allow_lds(place_fn, lds_place);
-  if (st != NTC_OK) return st;
-  const dim3 grid((unsigned)L.blocks), block(kBlock);
-  if (L.reg)
-    hipLaunchKernelGGL((bins_count<true, kWavesPerBlock>), grid, block, lds_count, stream, tex_id,
-                       (uint32_t)n, tex_to_dec, (uint32_t)n_textures, D, (uint32_t)L.chunk, hist,
-                       nullptr);
-  else
-    hipLaunchKernelGGL((bins_count<false, kWavesPerBlock>), grid, block, lds_count, stream, tex_id,
-                       (uint32_t)n, tex_to_dec, (uint32_t)n_textures, D, (uint32_t)L.chunk, hist,
-                       nullptr);
-  hipLaunchKernelGGL(bins_scan, dim3(D + 1), dim3(kScanThreads), 0, stream, hist, n_slices, D,
-                     bin_count, status, invalid_out);
-  if (L.reg)
-    hipLaunchKernelGGL(bins_place<true>, grid, block, lds_place, stream, tex_id, (uint32_t)n,
-                       tex_to_dec, (uint32_t)n_textures, D, (uint32_t)align, (uint32_t)L.chunk,
-                       hist, bin_count, bin_offset, perm);
-  else
-    hipLaunchKernelGGL(bins_place<false>, grid, block, lds_place, stream, tex_id, (uint32_t)n,
-                       tex_to_dec, (uint32_t)n_textures, D, (uint32_t)align, (uint32_t)L.chunk,
-                       hist, bin_count, bin_offset, perm);
-  return hip_status(hipGetLastError());
+  return st != NTC_OK ? st : hip_status(hipGetLastError());
 }
 
 size_t bins_status_bytes() { return kStatusWords * sizeof(uint32_t); }

@@ -156,6 +156,28 @@ def test_bins_workgroup_shapes(dev, oracle, n, D):
     assert bad > 0 and ntc.device_error(bins) == bad
 
 
+@pytest.mark.parametrize("D", [1, 2, 4, 5, 16, 17, 64, 65, 255, 256, 1023, 1024, 4096])
+@pytest.mark.parametrize("run", [1, 7, 300])
+def test_bins_row_ranking(dev, oracle, D, run):
+    """Around the id-bit counts the row ranking is compiled for, over streams whose
+    64-query rows hold many decoders (matched), a few (both ways in one batch) and
+    one or two (peeled), with ids out of range among them."""
+    rng = np.random.default_rng(31 * D + run)
+    T, n = D + 3, 40_007
+    t2d = np.minimum(rng.permutation(T), D).astype(np.uint32)  # three textures map past D
+    ids = rng.integers(0, T + 1, n // run + 1).astype(np.uint32)
+    ids[len(ids) // 2] = T  # at least one run out of range
+    tex = np.repeat(ids, run)[:n]
+    say(f"[bins-rows] D={D} run={run}")
+    bins = ntc.build_bins(torch.from_numpy(tex.view(np.int32)).to(dev),
+                          torch.from_numpy(t2d.view(np.int32)).to(dev), D, n_textures=T)
+    cnt, off, perm, bad = oracle.build_bins(tex, t2d, D, 64, n_textures=T)
+    assert np.array_equal(u32(bins.bin_count), cnt)
+    assert np.array_equal(u32(bins.bin_offset), off)
+    assert np.array_equal(u32(bins.perm)[: off[-1]], perm)
+    assert ntc.device_error(bins) == bad > 0
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_bins_unaligned_ids(dev, oracle, shift):
     """tex_id that does not start on a 16-byte boundary (a slice of a larger array)."""
