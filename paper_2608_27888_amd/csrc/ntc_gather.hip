@@ -5,9 +5,14 @@
 // consumes: the same device functions compute them, interpolation in packed
 // fp16.
 //
-// One lane per query, grid stride.  Each lane loads its query, its 2x2 taps per
-// level as 16-byte pieces of texel rows, interpolates, and writes its row with
-// 16-byte stores (fp32 rows: the fp16 values widened, exactly).
+// One wave per 64 queries, grid stride.  Each lane loads its query, its 2x2 taps
+// per level as 16-byte pieces of texel rows and interpolates; the rows then pass
+// through LDS (wave private, fp16) so that a store instruction writes 1 KB of
+// consecutive row pieces, 16 bytes a lane (fp32 rows: the fp16 values widened,
+// exactly).  What bounds it: the written rows (64 bytes a query at 2 x 16 fp16
+// channels) and the L1's tap traffic.  Storing each lane's own row, 16 bytes
+// every 64 or more, touched 32 lines an instruction: 67.4 us for the 1080p frame's fp16
+// rows; through LDS, non-temporal, 31.0 us (fp32 rows 111 -> 49 us).
 #include "ntc_decode_kernels.h"
 
 namespace ntc {
@@ -15,26 +20,48 @@ namespace {
 
 template <int NL, int CH, bool MIP, bool F16>
 __global__ void __launch_bounds__(kBlock) gather_rows(const DecodeArgs a) {
-  constexpr int F = NL * CH;  // features per row, a multiple of 8
-  const uint64_t stride = (uint64_t)gridDim.x * kBlock;
-  for (uint64_t i = (uint64_t)blockIdx.x * kBlock + threadIdx.x; i < a.n; i += stride) {
-    const Query qq = validate(a, load_query<NL, MIP>(a, (uint32_t)i, true));
+  constexpr int F = NL * CH;           // features per row, a multiple of 8
+  constexpr int kStride = F / 2 + 4;   // words of an LDS row: odd in 16-byte pieces, so the
+                                       // lanes' rows start on different banks
+  static_assert(F % 16 == 0, "an even number of 16-byte pieces a row");
+  __shared__ __attribute__((aligned(16))) uint32_t rows[kWavesPerBlock][kWave * kStride];
+  const uint32_t lane = lane_id();
+  uint32_t *mine = rows[threadIdx.x / kWave];
+  const uint64_t n_tiles = ((uint64_t)a.n + kWave - 1) / kWave;
+  const uint64_t stride = (uint64_t)gridDim.x * kWavesPerBlock;
+  for (uint64_t t = (uint64_t)blockIdx.x * kWavesPerBlock +
+                    __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+       t < n_tiles; t += stride) {
+    const uint64_t q0 = t * kWave;
+    const Query qq = validate(a, load_query<NL, MIP>(a, (uint32_t)(q0 + lane), q0 + lane < a.n));
     uint32_t x[F / 2];
     gather<NL, CH, 0, MIP>(a, qq, x);  // an invalid query samples texture 0
-    if (!qq.valid) continue;
-    if constexpr (F16) {
-      uint4 *row = (uint4 *)((uint16_t *)a.out + i * F);
+    const uint64_t valid = ballot(qq.valid);
+    // a wave's LDS operations execute in order: the previous tile's reads come
+    // before these writes, and the reads below after them
 #pragma unroll
-      for (int k = 0; k < F / 8; ++k)
-        row[k] = make_uint4(x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]);
-    } else {
-      float4 *row = (float4 *)((float *)a.out + i * F);
+    for (int k = 0; k < F / 8; ++k)
+      *(u32x4 *)(mine + lane * kStride + 4 * k) =
+          u32x4{x[4 * k], x[4 * k + 1], x[4 * k + 2], x[4 * k + 3]};
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    constexpr int P = F16 ? F / 8 : F / 4;  // 16-byte pieces of a row in memory
+    u32x4 *out = (u32x4 *)a.out + q0 * P;
 #pragma unroll
-      for (int k = 0; k < F / 4; ++k) {
-        const half2v p = as_h2(x[2 * k]), r = as_h2(x[2 * k + 1]);
-        row[k] = make_float4((float)p[0], (float)p[1], (float)r[0], (float)r[1]);
+    for (int i = 0; i < P; ++i) {
+      const uint32_t p = (uint32_t)i * kWave + lane, row = p / P, piece = p % P;
+      u32x4 v;
+      if constexpr (F16) {
+        v = *(const u32x4 *)(mine + row * kStride + 4 * piece);
+      } else {
+        const u32x2 h = *(const u32x2 *)(mine + row * kStride + 2 * piece);
+        const half2v lo = as_h2(h[0]), hi = as_h2(h[1]);
+        v = __builtin_bit_cast(u32x4, floatx4{(float)lo[0], (float)lo[1], (float)hi[0], (float)hi[1]});
       }
+      if ((valid >> row) & 1) __builtin_nontemporal_store(v, out + p);
     }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
   }
 }
 
