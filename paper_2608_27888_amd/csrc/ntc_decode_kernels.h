@@ -160,15 +160,29 @@ struct LdsNet : Net<NL, CH, PE, HID, NH> {
   }
 };
 
+// Bytes of the LDS cache of decoders below.
+constexpr int kCacheBytes = 150 * 1024;
+
 // A decoder whose weights this wave holds in registers and whose biases lie in
-// the wave's own LDS region.
+// LDS.
 template <int NL, int CH, int PE, int HID, int NH>
 struct RegNet : Net<NL, CH, PE, HID, NH> {
   using N = Net<NL, CH, PE, HID, NH>;
   half8 w[N::kFrags];
-  float *lds;  // N::kBiases floats
+  float *lds;  // the wave's own region, N::kBiases floats
+  const float *held;  // biases of the decoder in w: there, or in a cache slot
   __device__ __forceinline__ half8 weight(int f) const { return w[f]; }
-  __device__ __forceinline__ const float *biases() const { return lds; }
+  __device__ __forceinline__ const float *biases() const { return held; }
+  // every fragment has arrived when this returns: a load left pending into the
+  // caller's loop would be waited for on the path that loads nothing
+  __device__ __forceinline__ void arrived() {
+#pragma unroll
+    for (int f = 0; f < N::kFrags; ++f) {
+      u32x4 v = __builtin_bit_cast(u32x4, w[f]);
+      asm volatile("" : "+v"(v));
+      w[f] = as_half8(v);
+    }
+  }
   // Loads decoder `dec`: every load is issued before any is used.
   __device__ __forceinline__ void load(const DecodeArgs &a, uint32_t dec) {
     const uint16_t *p = a.params + (size_t)dec * (size_t)a.dec_stride;
@@ -182,14 +196,7 @@ struct RegNet : Net<NL, CH, PE, HID, NH> {
     }
 #pragma unroll
     for (int f = 0; f < N::kFrags; ++f) w[f] = N::load_slice(p, a.out_dim, f, lane);
-    // every fragment has arrived when this returns: a load left pending into
-    // the caller's loop would be waited for on the path that loads nothing
-#pragma unroll
-    for (int f = 0; f < N::kFrags; ++f) {
-      u32x4 v = __builtin_bit_cast(u32x4, w[f]);
-      asm volatile("" : "+v"(v));
-      w[f] = as_half8(v);
-    }
+    arrived();
     // the wave's earlier reads of the region come before these writes, and its
     // later ones after: a wave's LDS operations execute in order
 #pragma unroll
@@ -199,6 +206,41 @@ struct RegNet : Net<NL, CH, PE, HID, NH> {
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
+    held = lds;
+  }
+
+  // A workgroup's LDS cache of decoders (stream mode): kSlots images, decoder d
+  // in slot d % kSlots, filled once by the first wave that misses there and
+  // never replaced, so a filled slot is read without a lock and no wave waits
+  // for another.  A tag is kEmpty, kFilling or the decoder + 1.
+  static constexpr uint32_t kSlots = (uint32_t)(kCacheBytes / N::kImageBytes);
+  static constexpr uint32_t kEmpty = 0u, kFilling = 0xFFFFFFFFu;
+  __device__ __forceinline__ void load_cached(const DecodeArgs &a, uint32_t dec, uint32_t *tags,
+                                              uint32_t *images) {
+    const int lane = (int)lane_id();
+    const uint32_t slot = dec % kSlots;
+    uint32_t *image = images + (size_t)slot * (N::kImageBytes / 4);
+    const uint32_t tag = __builtin_amdgcn_readfirstlane(
+        __hip_atomic_load(&tags[slot], __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP));
+    if (tag == dec + 1) {
+#pragma unroll
+      for (int f = 0; f < N::kFrags; ++f)
+        w[f] = as_half8(*(const u32x4 *)(image + f * 256 + lane * 4));
+      arrived();
+      held = (const float *)image + N::kBiasOff;
+      return;
+    }
+    load(a, dec);
+    if (tag != kEmpty) return;
+    uint32_t was = kFilling;
+    if (lane == 0) was = atomicCAS(&tags[slot], kEmpty, kFilling);
+    if (__builtin_amdgcn_readfirstlane(was) != kEmpty) return;
+#pragma unroll
+    for (int f = 0; f < N::kFrags; ++f)
+      *(u32x4 *)(image + f * 256 + lane * 4) = __builtin_bit_cast(u32x4, w[f]);
+    for (int k = lane; k < N::kBiases; k += kWave) ((float *)image)[N::kBiasOff + k] = lds[k];
+    if (lane == 0)
+      __hip_atomic_store(&tags[slot], dec + 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
   }
 };
 
@@ -1116,30 +1158,38 @@ __device__ __forceinline__ uint32_t decoder_of(const DecodeArgs &a, const Query 
 // Stream decode with the weights in registers (64-wide decoders).  Every wave
 // walks a contiguous run of tiles and keeps the last decoder it used: a tile
 // takes the held decoder first, then loads each other one it needs, so a run
-// over one material loads nothing.  What bounds it is the latency of those
-// loads and, on frames of one material, what bounds the binned decode.  1080p
-// frame of 16 decoders: 193 us before, when every wave read each fragment of each
-// pass through the caches.
+// over one material loads nothing.  The other loads come from an LDS cache of
+// decoders where the workgroup has one (`cached`), else from the parameter
+// blocks.  What bounds it is the latency of those loads and, on frames of one
+// material, what bounds the binned decode.  1080p frame of 16 decoders: 192 us
+// when every wave read each fragment of each pass through the caches, 129 with
+// the held decoder, 88 with the LDS cache.
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__(kThreads, 2) decode_stream_reg(const DecodeArgs a) {
+__global__ void __launch_bounds__(kThreads, 2) decode_stream_reg(const DecodeArgs a, uint32_t cached) {
   using S = Shape<NL, CH, PE, HID>;
   using N = Net<NL, CH, PE, HID, NH>;
+  using R = RegNet<NL, CH, PE, HID, NH>;
   constexpr bool AHEAD = kTapsAhead<NL, CH, PE, HID, NH, MIP>;
   constexpr bool WIDE = kWideRows<STORE>;
   __shared__ __attribute__((aligned(16))) float biases[kWaves][N::kBiases];
+  __shared__ uint32_t tags[R::kSlots];
+  extern __shared__ __attribute__((aligned(16))) uint32_t images[];  // cached: kSlots images
   const uint32_t lane = lane_id();
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
   const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
   const uint32_t n_tiles = (uint32_t)(((uint64_t)a.n + kWave - 1) / kWave);
   const uint32_t nw = blockDim.x / kWave;  // waves of this workgroup, at most kWaves
+  if (threadIdx.x < R::kSlots) tags[threadIdx.x] = R::kEmpty;
+  __syncthreads();
   const uint64_t waves = (uint64_t)gridDim.x * nw;
   const uint64_t me = (uint64_t)xcd_local_block(blockIdx.x, gridDim.x) * nw + w;
   const uint32_t t_beg = (uint32_t)(n_tiles * me / waves);
   const uint32_t t_end = (uint32_t)(n_tiles * (me + 1) / waves);
   if (t_beg >= t_end) return;
   auto query_of = [&](uint32_t t) { return load_query<NL, MIP>(a, t * kWave + lane, t < t_end); };
-  RegNet<NL, CH, PE, HID, NH> net;
+  R net;
   net.lds = biases[w];
+  net.held = biases[w];
   uint32_t held = kNoDecoder;
   Query cur = query_of(t_beg);
   Query q_next = query_of(t_beg + 1);
@@ -1169,7 +1219,8 @@ __global__ void __launch_bounds__(kThreads, 2) decode_stream_reg(const DecodeArg
       if (!mine) {
         held = read_lane(dq, (uint32_t)__builtin_ctzll(todo));
         mine = ballot(dq == held);
-        net.load(a, held);
+        if (cached) net.load_cached(a, held, tags, images);
+        else net.load(a, held);
       }
       floatx4 y[4];
       mlp<NL, CH, PE, HID, NH, LEAKY>(net, xb, y, a.slope_h2);

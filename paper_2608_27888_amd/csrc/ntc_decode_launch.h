@@ -46,12 +46,21 @@ int launch_shape(const DecodeArgs &a, hipStream_t stream) {
     blocks = (tiles + waves - 1) / waves;
     if (blocks > cap * (kWaves / waves)) blocks = cap * (kWaves / waves);
     const dim3 grid((unsigned)blocks), threads((unsigned)waves * kWave);
-    if (a.bin_offset)
+    if (a.bin_offset) {
       hipLaunchKernelGGL((decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
                          0, stream, a);
-    else
+    } else {
+      // the decoder cache takes a CU's LDS, so it goes with the widest workgroups
+      // (one per CU anyway) and pays only where there is a decoder to switch to
+      using R = RegNet<NL, CH, PE, HID, NH>;
+      const bool cached = waves == kWaves && a.n_decoders > 1;
+      const size_t lds = cached ? (size_t)R::kSlots * N::kImageBytes : 0;
+      if (cached &&
+          hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return NTC_ERR_HIP;
       hipLaunchKernelGGL((decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
-                         0, stream, a);
+                         lds, stream, a, cached ? 1u : 0u);
+    }
   } else {
     const uint32_t image_bytes = ((uint32_t)N::kImageBytes + 15u) & ~15u;
     const void *fn = a.bin_offset

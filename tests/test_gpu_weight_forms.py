@@ -83,6 +83,25 @@ def test_workgroup_widths_and_deal(dev, oracle, tiles, D):
     assert np.abs(got[pick] - oracle.decode(part)).max() <= TOL
 
 
+@pytest.mark.parametrize("levels,ch,nh,out,octaves,mip", [
+    (2, 16, 1, 7, 4, False),     # 18 fragments: 8 cached decoders
+    (3, 16, 2, 3, 0, True),      # 26 fragments: 5
+])
+@pytest.mark.parametrize("D", [4, 40])
+def test_stream_decoder_cache(dev, oracle, levels, ch, nh, out, octaves, mip, D):
+    """A stream long enough for the workgroups' decoder cache, with fewer decoders
+    than it holds and with more (slots shared by several, filled by one)."""
+    n = 1025 * 64 + 5
+    w = workload(50 + D, n, levels, ch, 64, nh, out, octaves, mip, T=60, D=D)
+    print(f"[cache] dims={w.dims} D={D}", file=sys.stderr, flush=True)
+    got = both(dev, w).cpu().numpy()
+    pick = np.unique(np.linspace(0, n - 1, 4000).astype(np.int64))
+    part = W.Workload("part", w.n_textures, w.res, w.channels, w.latents, D, w.dims, w.params,
+                      w.tex_to_dec, w.tex_id[pick].copy(), w.uv[pick].copy(),
+                      None if w.mip is None else w.mip[pick].copy(), None, {}, octaves)
+    assert np.abs(got[pick] - oracle.decode(part)).max() <= TOL
+
+
 @pytest.mark.parametrize("hid", [64, 128])
 def test_non_finite_latents_stay_in_their_queries(dev, hid):
     """Infinities, NaN and overflowing activations of one texture change no row of
