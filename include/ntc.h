@@ -281,10 +281,10 @@ typedef struct {
  *     A query whose bilinear quad differs from the previous query's in the
  *     tile leads; each leader's quad is loaded once, by several lanes, into a
  *     wave-private LDS region (prefetched one tile ahead), and every query
- *     reads its taps from there.  The MLP then runs on 16x16x32 MFMAs.
+ *     reads its taps from there; the MLP is the same.
  *     Binned decode with the MFMA engine only, 2 levels, no mip and output
  *     widths up to 8 (NTC_ERR_UNSUPPORTED otherwise).  Results agree with the
- *     direct gather within rounding (the MFMA shape differs), not bit for bit.
+ *     direct gather within rounding.
  */
 #define NTC_GATHER_DIRECT 0
 #define NTC_GATHER_STAGED 1

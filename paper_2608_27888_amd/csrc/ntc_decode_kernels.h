@@ -908,6 +908,16 @@ template <int NL, int CH, int PE, int HID, int NH, bool MIP>
 constexpr bool kTapsAhead =
     kRegWeights<HID> && !MIP && NL * CH <= 32 && Net<NL, CH, PE, HID, NH>::kFrags <= 18;
 
+// Waves per workgroup, at most, and per SIMD of the binned kernel with the weights
+// in registers.  A tile that gathers when it starts waits for its taps; blending
+// 2 levels by mip fits 168 VGPRs, so three waves a SIMD, in workgroups of 4, hide
+// more of that wait than two (a 2255 x 1273 frame of 2 decoders: 103.1 -> 95.4 us;
+// 97.9 before the weights were held in registers).
+template <int NL, int NH, bool MIP>
+constexpr int kRegWaves = MIP && NL == 2 && NH == 1 ? 4 : kWaves;
+template <int NL, int NH, bool MIP>
+constexpr int kRegWavesPerSimd = MIP && NL == 2 && NH == 1 ? 3 : 2;
+
 // Binned decode with the weights in registers.  A workgroup takes a contiguous
 // range of tiles and deals them to its waves from a counter in LDS, each wave
 // on its own: it loads a decoder when its next tile's bin differs, with no
@@ -916,15 +926,16 @@ constexpr bool kTapsAhead =
 // clustered frame; from the counter the pass (binning and decode) takes 200.0
 // instead of 205.4 us, the 1080p one 54.4 instead of 55.5.
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__(kThreads, 2) decode_binned_reg(const DecodeArgs a) {
+__global__ void __launch_bounds__((kRegWaves<NL, NH, MIP> * kWave), (kRegWavesPerSimd<NL, NH, MIP>))
+decode_binned_reg(const DecodeArgs a) {
   using S = Shape<NL, CH, PE, HID>;
   using N = Net<NL, CH, PE, HID, NH>;
   constexpr bool AHEAD = kTapsAhead<NL, CH, PE, HID, NH, MIP>;
   constexpr bool WIDE = kWideRows<STORE>;
-  __shared__ __attribute__((aligned(16))) float biases[kWaves][N::kBiases];
+  __shared__ __attribute__((aligned(16))) float biases[kRegWaves<NL, NH, MIP>][N::kBiases];
   const uint32_t lane = lane_id();
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint32_t nw = blockDim.x / kWave;  // waves of this workgroup, at most kWaves
+  const uint32_t nw = blockDim.x / kWave;  // waves of this workgroup, at most kRegWaves
   const uint32_t D = (uint32_t)a.n_decoders;
   const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
   // tiles of the permutation; never more than the buffer holds

@@ -37,14 +37,15 @@ int launch_shape(const DecodeArgs &a, hipStream_t stream) {
     const void *fn = a.bin_offset
                          ? (const void *)decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>
                          : (const void *)decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
-    const uint64_t cap = resident_groups(fn, kThreads, 0);  // workgroups of kWaves waves
+    const uint64_t widest = a.bin_offset ? kRegWaves<NL, NH, MIP> : kWaves;
+    const uint64_t cap = resident_groups(fn, (int)widest * kWave, 0);  // workgroups of that width
     // Waves share nothing but the deal of tiles, so a call that does not fill the
     // chip takes narrower workgroups and reaches every CU (65,536 queries: 129
     // workgroups of 8 waves sit on half of the 256 CUs).
-    uint64_t waves = kWaves;
+    uint64_t waves = widest;
     while (waves > 1 && tiles <= cap * waves / 2) waves /= 2;
     blocks = (tiles + waves - 1) / waves;
-    if (blocks > cap * (kWaves / waves)) blocks = cap * (kWaves / waves);
+    if (blocks > cap * (widest / waves)) blocks = cap * (widest / waves);
     const dim3 grid((unsigned)blocks), threads((unsigned)waves * kWave);
     if (a.bin_offset) {
       hipLaunchKernelGGL((decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
