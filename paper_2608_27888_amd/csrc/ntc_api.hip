@@ -313,6 +313,15 @@ size_t ntc_kmeans_workspace_bytes(int32_t m, int32_t max_iter) {
 int ntc_kmeans(const float *features, int32_t n, int32_t dim, int32_t m, const uint32_t *init,
                int32_t max_iter, uint32_t *assign, double *centroids, uint32_t *counts,
                void *workspace, size_t workspace_bytes, void *stream) {
+  return ntc_internal_kmeans(features, n, dim, m, init, max_iter, assign, centroids, counts,
+                             workspace, workspace_bytes, stream, 0, 0);
+}
+
+int ntc_internal_kmeans(const float *features, int32_t n, int32_t dim, int32_t m,
+                        const uint32_t *init, int32_t max_iter, uint32_t *assign,
+                        double *centroids, uint32_t *counts, void *workspace,
+                        size_t workspace_bytes, void *stream, int32_t persist_groups,
+                        int32_t held_back) {
   if (!features || !init || !assign || !centroids || !counts || !workspace) return NTC_ERR_ARG;
   if (n < 1 || n > NTC_KMEANS_MAX_POINTS || dim < 1 || dim > NTC_KMEANS_MAX_DIM || m < 1 ||
       m > n || m > NTC_MAX_DECODERS || max_iter < 1 || max_iter > NTC_KMEANS_MAX_ITER)
@@ -324,7 +333,7 @@ int ntc_kmeans(const float *features, int32_t n, int32_t dim, int32_t m, const u
   if (seeds.back() >= (uint32_t)n || std::adjacent_find(seeds.begin(), seeds.end()) != seeds.end())
     return NTC_ERR_ARG;
   return launch_kmeans(features, n, dim, m, init, max_iter, assign, centroids, counts, workspace,
-                       (hipStream_t)stream);
+                       (hipStream_t)stream, persist_groups, held_back);
 }
 
 int ntc_kmeans_result(const void *workspace, int32_t m, int32_t max_iter, int32_t *iterations,

@@ -16,23 +16,27 @@
 //            empty cluster keeps its centroid.  Sizes k_g go to counts[j].
 //
 // Where the work of an iteration is small (kPersistWork), one launch runs every
-// iteration on at most one workgroup per CU, with a grid-wide wait after the
-// assignment and after the update, and stops when no label changes; two launches
-// an iteration cost 3.4 us each on the queue, also after convergence (100
-// iterations of 512 textures x 512 dimensions into 16 groups: 690 of 715 us).
-// Every wait is bounded: a workgroup whose wait runs out returns, and the
-// kernel behind, one workgroup, runs the clustering again from the seeds when
-// the flags say that the first did not finish (its grid was not resident at
-// once, which another stream's long kernels can cause).  Same sums in the same
-// order on every path, so the results are the same bits.  Larger problems take
-// an assignment and an update launch per iteration, and a per-iteration flag
-// lets every launch after convergence return at once.
+// iteration on at most one workgroup per CU and stops when no label changes; two
+// launches an iteration cost 3.4 us each on the queue, also after convergence
+// (100 iterations of 512 textures x 512 dimensions into 16 groups: 690 of 715 us).
+// A unit of its work is a share of an iteration's assignment or update.  When all
+// its workgroups have started (they count themselves first), each keeps its own
+// units through all iterations: static units find their textures in the L2 again.
+// When some have not started within kStartTicks (another stream's long kernels can
+// hold them back), the units are claimed one by one instead, and nobody waits but
+// for units whose workgroups are running, so the launch ends however few of its
+// workgroups the device runs at once, and those that start late help with what is
+// left.  Same sums in the same order whoever computes a unit, so the results are
+// the same bits.  Larger problems take an assignment and an update launch per
+// iteration, and a per-iteration flag lets every launch after convergence return at
+// once.
 //
 // What bounds it: latency.  Per iteration of 512 x 512 into 16 groups the
 // assignment takes 8-10 us (two rounds of loads per 8 centroids), each wait
 // 3.5 us (the L2s are written back and invalidated) and the update 6-9 us (the
 // member rows of the largest cluster, added in order); 3 iterations and the
-// launches: 683 us before, 105 us now.  20,000 x 512 into 300 groups, 4
+// launches: 690 us with two launches an iteration, 124 now (129 when a kernel
+// behind the launch checked whether it had run to its end).  20,000 x 512 into 300 groups, 4
 // iterations on the launch-per-iteration path: 17.3 -> 7.0 ms.
 #include "ntc_internal.h"
 
@@ -43,8 +47,8 @@ namespace {
 // arithmetic is about 50 us on the whole chip, against 7 us for two launches).
 constexpr int64_t kPersistWork = (int64_t)1 << 28;
 constexpr int64_t kPersistPoints = 65536;  // update: every unit scans all labels
-constexpr int kPersistGroups = 256;        // workgroups, at most (fields below hold 1023)
-constexpr uint64_t kWaitTicks = 2000000;   // 20 ms of the 100 MHz counter
+constexpr int kPersistGroups = 256;        // units and workgroups, at most (fields below)
+constexpr uint64_t kStartTicks = 10000;    // 100 us of the 100 MHz counter
 constexpr int kAssignCols = 8;             // centroids a wave compares at once
 constexpr int kListRows = 16;              // update: labels a wave lists at once, in rows of 64
 constexpr int kListLen = kListRows * kWave;
@@ -56,35 +60,41 @@ struct Seeds {
   uint32_t v[kArgSeeds];
 };
 
-// flags[t] of iteration t: bits 0-9 workgroups past the assignment, bits 10-19
-// those that changed a label, bits 20-29 those past the update.  The
-// launch-per-iteration path and the one-workgroup kernel only set kChanged.
-constexpr uint32_t kField = 1023u;
-constexpr uint32_t kAssigned = 1u, kChanged = 1u << 10, kUpdated = 1u << 20;
-__host__ __device__ inline bool any_change(uint32_t flag) { return ((flag >> 10) & kField) != 0; }
+// flags[t] of iteration t.  The persistent launch: bits 0-9 claims (the units of
+// the assignment, then those of the update, then one past them from each
+// workgroup: at most 3 * kPersistGroups), bits 10-18 units assigned, bits 19-27
+// those of them that changed a label.  The launches per iteration set kChanged.
+constexpr uint32_t kClaim = 1u, kClaims = 1023u, kUnits = 511u;
+constexpr uint32_t kAssigned = 1u << 10, kChanged = 1u << 19;
+static_assert(3 * kPersistGroups <= kClaims && kPersistGroups <= kUnits, "fields of a flag word");
+__host__ __device__ inline bool any_change(uint32_t flag) { return (flag / kChanged & kUnits) != 0; }
+
+// The persistent launch's progress word: bits 0-20 units updated in all iterations,
+// bits 21-29 workgroups started, bit 31 units are claimed.
+constexpr uint32_t kUpdated = (1u << 21) - 1, kStarted = 1u << 21, kClaiming = 1u << 31;
+static_assert((int64_t)kPersistGroups * NTC_KMEANS_MAX_ITER <= kUpdated, "updates of a whole run");
+__host__ __device__ inline uint32_t started(uint32_t progress) { return progress / kStarted & kUnits; }
 
 struct Problem {
   const float *features;
   int32_t n, dim, m;
   double *centroids;
   uint32_t *assign, *counts, *flags;
+  uint32_t *progress;  // of the persistent launch
   int32_t max_iter;
 };
 
 // seeds NULL: they come by value.
-__device__ __forceinline__ void seed_centroids(const Problem &p, const Seeds &arg,
-                                               const uint32_t *seeds, uint32_t j) {
-  const uint32_t row = seeds ? seeds[j] : arg.v[j];
-  const float *x = p.features + (size_t)row * p.dim;
-  for (int k = threadIdx.x; k < p.dim; k += blockDim.x)
-    p.centroids[(size_t)j * p.dim + k] = (double)x[k];
-}
-
 __global__ void __launch_bounds__(kBlock)
 kmeans_seed(const Problem p, const Seeds arg, const uint32_t *__restrict__ seeds) {
-  seed_centroids(p, arg, seeds, blockIdx.x);
-  if (blockIdx.x == 0)
+  const uint32_t j = blockIdx.x, row = seeds ? seeds[j] : arg.v[j];
+  const float *x = p.features + (size_t)row * p.dim;
+  for (int k = threadIdx.x; k < p.dim; k += kBlock)
+    p.centroids[(size_t)j * p.dim + k] = (double)x[k];
+  if (j == 0) {
     for (int t = threadIdx.x; t < p.max_iter; t += kBlock) p.flags[t] = 0;
+    if (!seeds && threadIdx.x == 0) *p.progress = 0;
+  }
 }
 
 // Butterfly sums of kAssignCols values over the wave: the first three steps
@@ -244,73 +254,106 @@ __global__ void __launch_bounds__(kBlock) kmeans_update(const Problem p, int32_t
   update_centroids(p, blockIdx.x * kWavesPerBlock + w, gridDim.x * kWavesPerBlock, lists[w]);
 }
 
-// Adds `add` to *word for this workgroup and waits until the field at `shift`
-// holds gridDim.x, at most kWaitTicks; returns the word, or kTimedOut.  What
-// every workgroup wrote before its own call is visible after it.
-constexpr uint32_t kTimedOut = 0xFFFFFFFFu;
-__device__ uint32_t grid_wait(uint32_t *word, uint32_t add, int shift, uint32_t *shared) {
-  __syncthreads();
+// Adds to a word that workgroups share; returns its old value.
+__device__ __forceinline__ uint32_t add_shared(uint32_t *word, uint32_t v) {
+  return __hip_atomic_fetch_add(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ uint32_t read_shared(const uint32_t *word) {
+  return __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Waits until done(*word), starting from a value `v` that thread 0 has seen;
+// returns the word.  What was written before the marks in it is visible after.
+template <typename Done>
+__device__ __forceinline__ uint32_t wait_until(const uint32_t *word, uint32_t v, Done done,
+                                               uint32_t *said) {
+  __syncthreads();  // *said has been read
   if (threadIdx.x == 0) {
-    __threadfence();
-    uint32_t v = __hip_atomic_fetch_add(word, add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + add;
-    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
-    bool in = ((v >> shift) & kField) == gridDim.x;
-    while (!in && __builtin_amdgcn_s_memrealtime() - t0 < kWaitTicks) {
+    while (!done(v)) {
       __builtin_amdgcn_s_sleep(1);
-      v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      in = ((v >> shift) & kField) == gridDim.x;
+      v = read_shared(word);
     }
     __threadfence();
-    *shared = in ? v : kTimedOut;
+    *said = v;
   }
   __syncthreads();
-  return *shared;
+  return *said;
 }
 
-__global__ void __launch_bounds__(kBlock) kmeans_persistent(const Problem p) {
+// Counts this workgroup as started and waits until all `expected` have, or until
+// the time is up; returns whether units are claimed.  Every workgroup returns the
+// same: kClaiming is only ever set while some have not started.
+__device__ __forceinline__ bool start(uint32_t *progress, uint32_t expected, uint32_t *said) {
+  if (threadIdx.x == 0) {
+    const uint64_t t0 = __builtin_amdgcn_s_memrealtime();
+    uint32_t v = add_shared(progress, kStarted) + kStarted;
+    while (!(v & kClaiming) && started(v) != expected) {
+      if (__builtin_amdgcn_s_memrealtime() - t0 >= kStartTicks) {
+        const uint32_t old = atomicCAS(progress, v, v | kClaiming);
+        v = old == v ? v | kClaiming : old;
+      } else {
+        __builtin_amdgcn_s_sleep(1);
+        v = read_shared(progress);
+      }
+    }
+    *said = v & kClaiming;
+  }
+  __syncthreads();
+  return *said != 0;
+}
+
+// expected: workgroups of the launch.  Every wait ends.  Without claims all
+// workgroups are running and each marks its units of a phase before it waits for
+// the others'.  With claims a workgroup waits for the assignment of t only once its
+// claim in t lies past it, and for the update of t - 1 only once it has left t - 1,
+// with a claim past that: all units waited for are claimed, and their workgroups run
+// and wait, if at all, for an earlier phase.
+__global__ void __launch_bounds__(kBlock)
+kmeans_persistent(const Problem p, uint32_t a_units, uint32_t u_units, uint32_t expected) {
   __shared__ uint16_t lists[kWavesPerBlock][kListLen];
-  __shared__ uint32_t word[2];
+  __shared__ uint32_t said[3];
   const uint32_t w = threadIdx.x / kWave;
-  const uint32_t wave = blockIdx.x * kWavesPerBlock + w, n_waves = gridDim.x * kWavesPerBlock;
+  const bool claims = start(p.progress, expected, &said[2]);
+  uint32_t progress = 0;  // thread 0: as last seen
   for (int32_t t = 0; t < p.max_iter; ++t) {
-    const bool changed = __syncthreads_or(assign_points(p, wave, n_waves, t));
-    const uint32_t v = grid_wait(p.flags + t, kAssigned + (changed ? kChanged : 0u), 0, &word[0]);
-    if (v == kTimedOut || !any_change(v)) return;
-    update_centroids(p, wave, n_waves, lists[w]);
-    if (grid_wait(p.flags + t, kUpdated, 20, &word[1]) == kTimedOut) return;
-  }
-}
-
-// One workgroup: returns at once when kmeans_persistent (of `groups` workgroups)
-// ran to its end, else runs the clustering from the seeds.
-constexpr int kFinishThreads = kBlock;
-__global__ void __launch_bounds__(kFinishThreads)
-kmeans_finish(const Problem p, const Seeds arg, uint32_t groups) {
-  constexpr int kWaves = kFinishThreads / kWave;
-  __shared__ uint16_t lists[kWaves][kListLen];
-  __shared__ int32_t stop;
-  // first iteration after which the grid did not go on
-  if (threadIdx.x == 0) stop = p.max_iter;
-  __syncthreads();
-  for (int32_t t = threadIdx.x; t < p.max_iter; t += kFinishThreads) {
-    const uint32_t v = p.flags[t];
-    if ((v & kField) != groups || !any_change(v) || ((v >> 20) & kField) != groups)
-      atomicMin(&stop, t);
-  }
-  __syncthreads();
-  if (stop == p.max_iter) return;
-  const uint32_t at = p.flags[stop];
-  if ((at & kField) == groups && !any_change(at)) return;  // converged there
-  __syncthreads();
-  for (int32_t t = threadIdx.x; t < p.max_iter; t += kFinishThreads) p.flags[t] = 0;
-  for (int32_t j = 0; j < p.m; ++j) seed_centroids(p, arg, nullptr, (uint32_t)j);
-  const uint32_t w = threadIdx.x / kWave;
-  for (int32_t t = 0; t < p.max_iter; ++t) {
-    __syncthreads();
-    const bool changed = __syncthreads_or(assign_points(p, w, kWaves, t));
-    if (!changed) return;
-    if (threadIdx.x == 0) p.flags[t] = kChanged;
-    update_centroids(p, w, kWaves, lists[w]);
+    uint32_t *word = p.flags + t, seen = 0, unit = blockIdx.x;
+    if (claims) {
+      if (threadIdx.x == 0) said[0] = add_shared(word, kClaim) & kClaims;
+      __syncthreads();
+      unit = said[0];
+    }
+    if (t > 0 && unit < a_units)
+      wait_until(p.progress, progress,
+                 [&](uint32_t v) { return (v & kUpdated) == u_units * (uint32_t)t; }, &said[2]);
+    while (unit < a_units) {
+      const bool changed = __syncthreads_or(
+          assign_points(p, unit * kWavesPerBlock + w, a_units * kWavesPerBlock, t));
+      if (threadIdx.x == 0) {
+        const uint32_t mark = kAssigned + (changed ? kChanged : 0u) + (claims ? kClaim : 0u);
+        __threadfence();
+        const uint32_t old = add_shared(word, mark);
+        seen = old + mark;
+        said[1] = old & kClaims;
+      }
+      __syncthreads();
+      unit = claims ? said[1] : unit + expected;
+    }
+    const uint32_t all = wait_until(
+        word, seen, [&](uint32_t v) { return (v / kAssigned & kUnits) == a_units; }, &said[2]);
+    if (!any_change(all)) return;
+    if (!claims) unit = a_units + blockIdx.x;
+    while (unit < a_units + u_units) {
+      update_centroids(p, (unit - a_units) * kWavesPerBlock + w, u_units * kWavesPerBlock, lists[w]);
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        __threadfence();
+        progress = add_shared(p.progress, 1u) + 1u;
+        if (claims) said[1] = add_shared(word, kClaim) & kClaims;
+      }
+      __syncthreads();
+      unit = claims ? said[1] : unit + expected;
+    }
   }
 }
 
@@ -322,9 +365,11 @@ size_t kmeans_workspace_bytes(int32_t m, int32_t max_iter) {
 
 int launch_kmeans(const float *features, int32_t n, int32_t dim, int32_t m, const uint32_t *init,
                   int32_t max_iter, uint32_t *assign, double *centroids, uint32_t *counts,
-                  void *workspace, hipStream_t stream) {
-  uint32_t *dinit = (uint32_t *)workspace;  // [m] seed textures, then [max_iter] flags
-  const Problem p = {features, n, dim, m, centroids, assign, counts, dinit + m, max_iter};
+                  void *workspace, hipStream_t stream, int32_t persist_groups,
+                  int32_t held_back) {
+  // [m] seed textures (passed by value: word 0 the progress), then [max_iter] flags
+  uint32_t *dinit = (uint32_t *)workspace;
+  const Problem p = {features, n, dim, m, centroids, assign, counts, dinit + m, dinit, max_iter};
   // the seed list is the caller's host memory: by value where it fits a kernel's
   // arguments, else copied before this call returns
   Seeds arg = {};
@@ -341,16 +386,22 @@ int launch_kmeans(const float *features, int32_t n, int32_t dim, int32_t m, cons
   const int64_t units = (int64_t)m * ((dim + kWave - 1) / kWave);
   const auto groups_of = [](int64_t waves) { return (waves + kWavesPerBlock - 1) / kWavesPerBlock; };
   if (by_value && n <= kPersistPoints && (int64_t)n * m <= kPersistWork / dim) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      return NTC_ERR_HIP;
-    int64_t groups = groups_of(n > units ? n : units);
-    const int64_t most = cus < kPersistGroups ? cus : kPersistGroups;
-    if (groups > most) groups = most;
-    hipLaunchKernelGGL(kmeans_persistent, dim3((unsigned)groups), dim3(kBlock), 0, stream, p);
-    hipLaunchKernelGGL(kmeans_finish, dim3(1), dim3(kFinishThreads), 0, stream, p, arg,
-                       (uint32_t)groups);
+    const auto units_of = [&](int64_t waves) {
+      return groups_of(waves) < kPersistGroups ? groups_of(waves) : (int64_t)kPersistGroups;
+    };
+    const int64_t a_units = units_of(n), u_units = units_of(units);
+    const int64_t share = a_units > u_units ? a_units : u_units;
+    int64_t groups = persist_groups;
+    if (groups < 1) {
+      int dev = 0, cus = 0;
+      if (hipGetDevice(&dev) != hipSuccess ||
+          hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return NTC_ERR_HIP;
+      groups = share < cus ? share : cus;
+    }
+    if (groups > kPersistGroups) groups = kPersistGroups;
+    hipLaunchKernelGGL(kmeans_persistent, dim3((unsigned)groups), dim3(kBlock), 0, stream, p,
+                       (uint32_t)a_units, (uint32_t)u_units, (uint32_t)(groups + held_back));
     return hip_status(hipGetLastError());
   }
   const int64_t most_units = (int64_t)1 << 20;  // grid stride beyond

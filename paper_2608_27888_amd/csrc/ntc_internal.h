@@ -125,14 +125,25 @@ template <int NL, int CH, int PE, int HID>
 int launch_decode_fma_shape(const DecodeArgs &a, hipStream_t stream);
 
 // k-means of per-texture features (ntc_cluster.hip).  Workspace: m seed
-// indices (m > 256 only), then one u32 flag word per iteration.
+// indices (m > 256; else the first is the persistent launch's progress), then one
+// u32 flag word per iteration.  For the persistent launch, where the problem takes
+// it: persist_groups workgroups (0: as many as fill the device) that count on
+// held_back more, which never start.  The results depend on neither.
 size_t kmeans_workspace_bytes(int32_t m, int32_t max_iter);
 int launch_kmeans(const float *features, int32_t n, int32_t dim, int32_t m, const uint32_t *init,
                   int32_t max_iter, uint32_t *assign, double *centroids, uint32_t *counts,
-                  void *workspace, hipStream_t stream);
+                  void *workspace, hipStream_t stream, int32_t persist_groups,
+                  int32_t held_back);
 int read_kmeans_state(const void *workspace, int32_t m, int32_t max_iter, int32_t *iterations,
                       int32_t *converged, hipStream_t stream);
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? NTC_OK : NTC_ERR_HIP; }
 
 }  // namespace ntc
+
+// Not part of the ABI, for the tests: ntc_kmeans with launch_kmeans' last two.
+extern "C" int ntc_internal_kmeans(const float *features, int32_t n, int32_t dim, int32_t m,
+                                   const uint32_t *init, int32_t max_iter, uint32_t *assign,
+                                   double *centroids, uint32_t *counts, void *workspace,
+                                   size_t workspace_bytes, void *stream, int32_t persist_groups,
+                                   int32_t held_back);

@@ -10,6 +10,7 @@ so a label decided by a near-exact tie could differ: the tests check that the
 oracle's margin between the nearest and second-nearest centroid is far above
 float64 rounding before they require identical labels.
 """
+import ctypes
 import sys
 
 import numpy as np
@@ -81,6 +82,45 @@ def test_kmeans_path_edges(dev, oracle, n, m, dim):
     f, _ = W.texture_features(100 + n, n, m, dim, spread=0.6)
     say(f"[kmeans-edges] n={n} m={m} dim={dim}")
     check(dev, oracle, f, W.kmeans_seeds(7, n, m), max_iter=12)
+
+
+@pytest.mark.parametrize("held_back", [0, 1])
+@pytest.mark.parametrize("groups", [1, 3, 256])
+@pytest.mark.parametrize("n,m,dim,max_iter", [
+    (3, 2, 5, 10),           # one unit of work, so most of 256 workgroups claim none
+    (65, 9, 65, 2),          # stopped before convergence
+    (700, 6, 96, 100),       # 175 units
+    (5000, 40, 130, 30),     # 256 units
+])
+def test_kmeans_any_number_of_workgroups(dev, oracle, groups, held_back, n, m, dim, max_iter):
+    """The persistent launch with fewer workgroups than units of work and with more,
+    all of them started (each keeps its units) or one of them never (held_back, as
+    when another stream's kernels keep it off the device: the units are claimed):
+    the oracle's labels, sizes, centroids, iterations and convergence, bit for bit."""
+    f, _ = W.texture_features(40 + n, n, m, dim, spread=0.6)
+    seeds = W.kmeans_seeds(9, n, m)
+    say(f"[kmeans-groups] groups={groups} held_back={held_back} n={n} m={m} dim={dim}")
+    P, i32 = ctypes.c_void_p, ctypes.c_int32
+    fn = ntc.lib().ntc_internal_kmeans
+    fn.argtypes, fn.restype = [P, i32, i32, i32, P, i32, P, P, P, P, ctypes.c_size_t, P, i32, i32], i32
+    x = torch.from_numpy(f).to(dev)
+    assign = torch.empty(n, dtype=torch.int32, device=dev)
+    centroids = torch.empty((m, dim), dtype=torch.float64, device=dev)
+    counts = torch.empty(m, dtype=torch.int32, device=dev)
+    wsb = ntc.lib().ntc_kmeans_workspace_bytes(m, max_iter)
+    ws = torch.full((wsb,), 255, dtype=torch.uint8, device=dev)
+    stream = P(torch.cuda.current_stream().cuda_stream)
+    assert fn(x.data_ptr(), n, dim, m, seeds.ctypes.data, max_iter, assign.data_ptr(),
+              centroids.data_ptr(), counts.data_ptr(), ws.data_ptr(), wsb, stream, groups, held_back) == 0
+    it, conv = i32(0), i32(0)
+    assert ntc.lib().ntc_kmeans_result(ws.data_ptr(), m, max_iter, ctypes.byref(it),
+                                       ctypes.byref(conv), stream) == 0
+    labels, c, sizes, oit, oconv = oracle.kmeans(f, seeds, max_iter)
+    assert margins_ok(f, c, labels)
+    assert np.array_equal(assign.cpu().numpy().view(np.uint32), labels)
+    assert np.array_equal(counts.cpu().numpy().view(np.uint32), sizes)
+    assert np.array_equal(centroids.cpu().numpy(), c)
+    assert (it.value, bool(conv.value)) == (oit, oconv)
 
 
 def test_kmeans_hand_worked_and_ties(dev, oracle):
