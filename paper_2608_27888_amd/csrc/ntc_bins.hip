@@ -87,12 +87,18 @@ __device__ __forceinline__ Slice slice_of(uint32_t b, uint32_t w, uint64_t chunk
 // uniform, base < end): lanes at or past `end` get kOutside, invalid queries
 // `invalid`.  Every id load is issued, then every map lookup, before any result
 // is used; the loads are unconditional (clamped into the slice), addressed from
-// one wave-uniform pointer with 32-bit lane offsets.
+// one wave-uniform pointer with 32-bit lane offsets.  ANEW: the offsets are formed
+// anew for every batch.  Where every row is matched a batch is one straight block,
+// and the compiler would keep them from one to the next: 68-72 registers in count
+// (of 16-wave workgroups one a CU instead of two) and spills in place (4K frame of
+// two decoders, binning 31.3 us against 28.6).
+template <bool ANEW>
 __device__ __forceinline__ void load_batch(const uint32_t *__restrict__ tex_id,
                                            const uint32_t *__restrict__ tex_to_dec,
                                            uint32_t n_textures, uint32_t n_decoders,
                                            uint32_t invalid, uint64_t base, uint64_t end,
                                            uint32_t lane, uint32_t (&d)[kBatchRows]) {
+  if constexpr (ANEW) asm volatile("" : "+v"(lane));
   const uint32_t *row = tex_id + base;
   const uint64_t left = end - base;
   const uint32_t lim = left < (uint64_t)kWaveQuantum ? (uint32_t)left : (uint32_t)kWaveQuantum;
@@ -125,8 +131,10 @@ __device__ __forceinline__ void load_batch(const uint32_t *__restrict__ tex_id,
 // row: 30.2 us peeling, 19.8 matching).  So with more than 16 decoders the first
 // row of a batch of 16 is peeled, and when it held more than kPeelMost decoders
 // the other rows are matched.  With at most 4 decoders (2 bits) every row is
-// matched (65,536 queries of 2 decoders: 13.1 -> 12.1 us); with 5 to 16 every row is
-// peeled (the choice alone cost the 4K clustered frame 2 us).
+// matched (65,536 random queries of 2 decoders: 13.7 -> 11.7 us; 4K frames of regions
+// are within 2 % of peeling: 27.0 us against 26.4 with two decoders, 29.1 against 28.5
+// with four, where a peeled first row that decides takes 29.4 and 31.0); with 5 to 16
+// every row is peeled (the choice alone cost the 4K clustered frame 2 us).
 constexpr uint32_t kPeelMost = 4;
 
 // Lanes of `valid` whose value equals v, compared in its low B bits; v may differ
@@ -157,7 +165,8 @@ __device__ __forceinline__ uint32_t popcount64(uint64_t m) {
 // Number of decoder-id bits the row functions are compiled for: the next of
 // these that holds D ids, or with LDS tables D + 1 (id D counts the invalid).
 constexpr int id_bits(uint32_t D) {
-  return D <= 1 ? 0 : D <= 4 ? 2 : D <= 16 ? 4 : D <= 64 ? 6 : D < 256 ? 8 : D < 1024 ? 10 : 13;
+  return D <= 1 ? 0 : D <= 2 ? 1 : D <= 4 ? 2 : D <= 16 ? 4 : D <= 64 ? 6 : D < 256 ? 8
+         : D < 1024 ? 10 : 13;
 }
 constexpr bool peels(int bits) { return bits > 2; }
 constexpr bool matches(int bits) { return bits <= 2 || bits > 4; }
@@ -208,8 +217,11 @@ __device__ __forceinline__ uint32_t match_row(uint32_t d, uint32_t &reg, uint32_
     const uint32_t rank = lanes_below(same);
     uint32_t at = 0;
     if constexpr (REG) {
-      at = B == 0 ? read_lane(reg, 0)
-                  : (uint32_t)__builtin_amdgcn_ds_bpermute((int)(d << 2), (int)reg);
+      // one bit: two lane reads instead of the LDS permutation's latency (4K frame of
+      // two decoders: 28.6 -> 27.0 us)
+      at = B == 0   ? read_lane(reg, 0)
+           : B == 1 ? (d & 1 ? read_lane(reg, 1) : read_lane(reg, 0))
+                    : (uint32_t)__builtin_amdgcn_ds_bpermute((int)(d << 2), (int)reg);
       reg += popcount64(row.equal(lane));
     } else {
       uint32_t old = 0;  // the first lane of each decoder reads and advances its value
@@ -270,7 +282,8 @@ bins_count(const uint32_t *__restrict__ tex_id, uint32_t n,
   uint32_t invalid = 0;
   for (uint64_t base = sl.beg; base < sl.end; base += kWaveQuantum) {
     uint32_t d[kBatchRows];
-    load_batch(tex_id, tex_to_dec, n_textures, n_decoders, n_decoders, base, sl.end, lane, d);
+    load_batch<!peels(B)>(tex_id, tex_to_dec, n_textures, n_decoders, n_decoders, base, sl.end,
+                          lane, d);
     if constexpr (REG) {
 #pragma unroll
       for (int j = 0; j < kBatchRows; ++j) {
@@ -393,7 +406,7 @@ bins_place(const uint32_t *__restrict__ tex_id, uint32_t n,
   // queries are marked as outside: they go nowhere.
   uint32_t d[kBatchRows];
   if (sl.beg < sl.end)
-    load_batch(tex_id, tex_to_dec, n_textures, D, kOutside, sl.beg, sl.end, lane, d);
+    load_batch<!peels(B)>(tex_id, tex_to_dec, n_textures, D, kOutside, sl.beg, sl.end, lane, d);
   // Padded bin offsets: thread i owns decoders [dlo, dhi).
   const uint32_t dper = (D + kBlock - 1) / kBlock;
   const uint32_t dlo = min(threadIdx.x * dper, D);
@@ -425,7 +438,7 @@ bins_place(const uint32_t *__restrict__ tex_id, uint32_t n,
   uint32_t cursors = REG && lane < D ? table[lane] : 0u;
   for (uint64_t base = sl.beg; base < sl.end; base += kWaveQuantum) {
     if (base != sl.beg)
-      load_batch(tex_id, tex_to_dec, n_textures, D, kOutside, base, sl.end, lane, d);
+      load_batch<!peels(B)>(tex_id, tex_to_dec, n_textures, D, kOutside, base, sl.end, lane, d);
     batch_rows<REG, true, B>(d, cursors, table, lane, [&](int j, uint32_t pos) {
       if (d[j] != kOutside) perm[pos] = (uint32_t)(base + (uint64_t)j * kWave + lane);
     });
@@ -455,7 +468,7 @@ bins_place_sum(const uint32_t *__restrict__ tex_id, uint32_t n,
   // queries are marked as outside: they go nowhere.
   uint32_t d[kBatchRows];
   if (sl.beg < sl.end)
-    load_batch(tex_id, tex_to_dec, n_textures, D, kOutside, sl.beg, sl.end, lane, d);
+    load_batch<!peels(B)>(tex_id, tex_to_dec, n_textures, D, kOutside, sl.beg, sl.end, lane, d);
   // Row r of tot (r = D: invalid queries): its total and its sum over the
   // workgroups before this one.  kSumLanes lanes take a row, kSumPer words
   // each, all loaded at once.
@@ -518,7 +531,7 @@ bins_place_sum(const uint32_t *__restrict__ tex_id, uint32_t n,
   if (lane < D) cursors = start[lane] + before[lane] + hist[(size_t)lane * n_slices + b * WAVES + w];
   for (uint64_t base = sl.beg; base < sl.end; base += kWaveQuantum) {
     if (base != sl.beg)
-      load_batch(tex_id, tex_to_dec, n_textures, D, kOutside, base, sl.end, lane, d);
+      load_batch<!peels(B)>(tex_id, tex_to_dec, n_textures, D, kOutside, base, sl.end, lane, d);
     batch_rows<true, true, B>(d, cursors, nullptr, lane, [&](int j, uint32_t pos) {
       if (d[j] != kOutside) perm[pos] = (uint32_t)(base + (uint64_t)j * kWave + lane);
     });
@@ -631,6 +644,7 @@ int launch_build_bins(const uint32_t *tex_id, int64_t n, const uint32_t *tex_to_
   int st = NTC_OK;
   switch (id_bits(D)) {
     case 0: L.sum ? launch_sum_waves<0>(c, L.waves) : (void)(st = launch_three<true, 0>(c)); break;
+    case 1: L.sum ? launch_sum_waves<1>(c, L.waves) : (void)(st = launch_three<true, 1>(c)); break;
     case 2: L.sum ? launch_sum_waves<2>(c, L.waves) : (void)(st = launch_three<true, 2>(c)); break;
     case 4: L.sum ? launch_sum_waves<4>(c, L.waves) : (void)(st = launch_three<true, 4>(c)); break;
     case 6: L.sum ? launch_sum_waves<6>(c, L.waves) : (void)(st = launch_three<true, 6>(c)); break;

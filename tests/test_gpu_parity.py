@@ -178,6 +178,24 @@ def test_bins_row_ranking(dev, oracle, D, run):
     assert ntc.device_error(bins) == bad > 0
 
 
+@pytest.mark.parametrize("D", [1, 2, 3])
+@pytest.mark.parametrize("n,run", [(65_601, 1), (2_200_001, 300), (4_300_001, 37)])
+def test_bins_few_decoders(dev, oracle, D, n, run):
+    """The forms that match every row (0, 1 and 2 id bits) on workgroups of 4, 8 and 16
+    waves, invalid ids among them."""
+    rng = np.random.default_rng(7 * D + run)
+    t2d = np.array([0, D - 1, 0, D], np.uint32)  # texture 3 maps past D, 4 is out of range
+    tex = np.repeat(rng.integers(0, 5, n // run + 1).astype(np.uint32), run)[:n]
+    say(f"[bins-few] D={D} n={n} run={run}")
+    bins = ntc.build_bins(torch.from_numpy(tex.view(np.int32)).to(dev),
+                          torch.from_numpy(t2d.view(np.int32)).to(dev), D, n_textures=4)
+    cnt, off, perm, bad = oracle.build_bins(tex, t2d, D, 64, n_textures=4)
+    assert np.array_equal(u32(bins.bin_count), cnt)
+    assert np.array_equal(u32(bins.bin_offset), off)
+    assert np.array_equal(u32(bins.perm)[: off[-1]], perm)
+    assert ntc.device_error(bins) == bad > 0
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_bins_unaligned_ids(dev, oracle, shift):
     """tex_id that does not start on a 16-byte boundary (a slice of a larger array)."""

@@ -1,0 +1,54 @@
+"""Registers and scratch of the built kernels, as the compiler reported them
+(paper_2608_27888_amd/libntc.kernels.json, written by the build): the launch shapes
+count on the occupancy, and a spilled register is memory traffic inside a loop."""
+import json
+
+import pytest
+
+from paper_2608_27888_amd import build
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    with open(build.KERNELS) as f:
+        return {name: used for per in json.load(f).values() for name, used in per.items()}
+
+
+def named(kernels, part):
+    found = {k: v for k, v in kernels.items() if part in k}
+    assert found, part
+    return found
+
+
+def test_report_is_read_whole():
+    report = """a.hip:3:1: warning: real [-Wsome]
+    3 | code
+      | ^
+In file included from b.hip:2:
+c.h:7:1: remark: Function Name: _Zk [-Rpass-analysis=kernel-resource-usage]
+    7 | __global__
+      | ^
+In file included from b.hip:2:
+c.h:7:1: remark:     VGPRs: 57 [-Rpass-analysis=kernel-resource-usage]
+    7 | __global__
+      | ^
+c.h:7:1: remark:     ScratchSize [bytes/lane]: 8 [-Rpass-analysis=kernel-resource-usage]
+    7 | __global__
+      | ^
+c.h:7:1: remark:     Dynamic Stack: False [-Rpass-analysis=kernel-resource-usage]
+    7 | __global__
+      | ^
+In file included from b.hip:2:
+c.h:9:1: warning: other [-Wsome]"""
+    used, rest = build.resources(report)
+    assert used == {"_Zk": {"VGPRs": 57, "ScratchSize": 8}}
+    assert rest == ["a.hip:3:1: warning: real [-Wsome]", "    3 | code", "      | ^",
+                    "In file included from b.hip:2:", "c.h:9:1: warning: other [-Wsome]"]
+
+
+def test_binning_runs_eight_waves_a_simd_without_scratch(kernels):
+    """Two 16-wave workgroups a CU need eight waves a SIMD: at most 64 registers."""
+    for part in ("bins_count", "bins_place"):
+        for name, used in named(kernels, part).items():
+            assert used["ScratchSize"] == 0, (name, used)
+            assert used["Occupancy"] == 8, (name, used)
