@@ -24,20 +24,21 @@
 // are the accumulator input of the first MFMA of each row block.  Every kernel
 // runs this one function (mlp), so binned and stream mode give the same bits.
 //
-// Why 16x16x32: the decode draws the chip into its power limit (1.7-1.9 GHz
-// measured inside the 4K clustered decode, 2.1 without its MFMAs or its LDS
-// weight reads), so its time follows the energy of a tile.  16x16x32 moves half
-// the accumulator bytes per flop of 32x32x16 and pads an 8-wide output layer to
-// 16 rows instead of 32: 161 -> 153 us on the 4K clustered frame, 50.7 -> 48 us
-// on the 1080p one.
+// Why 16x16x32: the decode's time follows the work of a tile (its clock is 1.7-1.9
+// GHz by wave timestamps, 2.1 without its MFMAs or its LDS weight reads).  16x16x32
+// moves half the accumulator bytes per flop of 32x32x16 and pads an 8-wide output
+// layer to 16 rows instead of 32: 161 -> 153 us on the 4K clustered frame, 50.7 -> 48
+// us on the 1080p one.
 //
-// Decoders with 64-wide hidden layers keep their weights in registers (14
-// fragments of 4 registers for 32-64-64-8), two waves per SIMD: no LDS reads
-// but the biases, no barriers, and the taps of the next tile are fetched a
-// whole MLP ahead.  Against weights read from LDS for every tile, four waves per
-// SIMD: 153 -> 148-151 us on the 4K clustered frame, 48 -> 45 us on the 1080p
-// one, 58 -> 52 us on the divergent one.  128-wide decoders (84 fragments for
-// 48-128-128-128-8) are staged in LDS, one image per workgroup.
+// Binned, a workgroup stages its decoder in LDS and every wave reads the fragments
+// there: four waves per SIMD for 64-wide decoders (LDS image about 15 KB), two for
+// 128-wide ones (84 fragments for 48-128-128-128-8, one image per CU).  Weights held in
+// registers (14 fragments of 4 registers for 32-64-64-8) leave two waves per SIMD, too
+// few wherever a tile does more between its MFMAs: at 1080p, 16 decoders, 2 x 8
+// channels with mip 70.4 us against 61.9 from LDS, fp16 RGB rows with LeakyReLU 72.5
+// against 64.1, two hidden layers 80.6 against 72.4; equal on the 4K clustered frame
+// (185).  In stream order, where each wave takes its own decoders, 64-wide ones are
+// held in registers.
 //
 // A second engine (decode_fma, end of the file) evaluates the MLP per lane with
 // vector dot products instead: the paper's Non-Shared FMA comparison.
@@ -888,171 +889,50 @@ __device__ __forceinline__ uint32_t bin_of_slot(const DecodeArgs &a, uint32_t D,
   return __builtin_amdgcn_readfirstlane(lo);
 }
 
-// Waves per workgroup of every kernel of the MFMA engine, two per SIMD: a wave
-// of a 64-wide decoder holds its weights and the next tile's taps (up to 256
-// VGPRs); a 128-wide decoder's LDS image (about 86 KB for 48-128-128-128-8)
-// allows one workgroup per CU.
+// Waves per workgroup of every kernel of the MFMA engine.
 constexpr int kWaves = 8;
 constexpr int kThreads = kWaves * kWave;
 
-// Weights in registers: 64-wide hidden layers (at most 26 fragments).
+// Waves per SIMD that the registers of the binned decode must allow: two workgroups
+// per CU, or one for 128-wide decoders.  At four some shapes spill (two hidden layers
+// with LeakyReLU, positional encoding: up to 60 bytes a lane) and are still faster
+// than at three, where none does (1080p, two hidden layers, LeakyReLU, RGB: 79.6 us
+// against 82.9 with 2 x 8 channels, 84.6 against 87.0 with 2 x 16).
+template <int HID>
+constexpr int kBinnedWavesPerSimd = HID == 64 ? 4 : 2;
+
+// Weights in registers: stream order, 64-wide hidden layers (at most 26 fragments).
 template <int HID>
 constexpr bool kRegWeights = HID == 64;
 
-// The taps of the next tile are fetched before this tile's MLP where they and
-// the weights leave the MLP its registers: up to 64 registers of taps (2 levels of
-// 16 channels) and 18 fragments.  Otherwise a tile gathers when it starts:
+// Taps ahead.  Stream: the taps of the next tile are fetched before this tile's MLP
+// where they and the weights leave it its registers: up to 64 registers of taps (2
+// levels of 16 channels) and 18 fragments.  Otherwise a tile gathers when it starts:
 // carrying 3 levels' taps (96 registers) beside the weights spilled (1080p frame of
-// 48-64-64-8: 147 us against 83 before).
+// 48-64-64-8: 147 us against 83).
 template <int NL, int CH, int PE, int HID, int NH, bool MIP>
-constexpr bool kTapsAhead =
-    kRegWeights<HID> && !MIP && NL * CH <= 32 && Net<NL, CH, PE, HID, NH>::kFrags <= 18;
+constexpr bool kStreamTapsAhead =
+    kRegWeights<HID> && !MIP && NL * CH <= 32 &&
+    Net<NL, CH, PE, HID, NH>::kFrags <= 18;
+// Binned: fetched before this tile's stores for 128-wide decoders; with four waves a
+// SIMD the other waves hide a gather at the tile's start (1080p one material, passes
+// of 51.2 us against 52.9 fetched ahead; 3 levels, 70.9 against 86).
+template <int HID, bool MIP>
+constexpr bool kBinnedTapsAhead = !MIP && HID > 64;
 
-// Waves per workgroup, at most, and per SIMD of the binned kernel with the weights
-// in registers.  A tile that gathers when it starts waits for its taps; blending
-// 2 levels by mip fits 168 VGPRs, so three waves a SIMD, in workgroups of 4, hide
-// more of that wait than two (a 2255 x 1273 frame of 2 decoders: 103.1 -> 95.4 us;
-// 97.9 before the weights were held in registers).
-template <int NL, int NH, bool MIP>
-constexpr int kRegWaves = MIP && NL == 2 && NH == 1 ? 4 : kWaves;
-template <int NL, int NH, bool MIP>
-constexpr int kRegWavesPerSimd = MIP && NL == 2 && NH == 1 ? 3 : 2;
-
-// Binned decode with the weights in registers.  A workgroup takes a contiguous
-// range of tiles and deals them to its waves from a counter in LDS, each wave
-// on its own: it loads a decoder when its next tile's bin differs, with no
-// barrier.  Waves w and w + 4 share a SIMD, which issues the older one first:
-// dealt evenly, waves 0-3 ended after 117 us and waves 4-7 after 170 us of the 4K
-// clustered frame; from the counter the pass (binning and decode) takes 200.0
-// instead of 205.4 us, the 1080p one 54.4 instead of 55.5.
+// Binned decode with the weights in LDS: a workgroup walks a contiguous range of
+// tiles, one a wave at a time inside one bin, restaging the decoder when the bin
+// changes.  split: twice the tiles for the first workgroup dispatched to each CU
+// (blockIdx < gridDim / 2) of two: the SIMDs issue the older waves first, so two with
+// equal work finish a third apart and the second runs its last third on half the
+// waves (4K frame of 2 x 16 channels with mip 214.9 -> 207.2 us, 1080p 70.0 -> 67.7).
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__((kRegWaves<NL, NH, MIP> * kWave), (kRegWavesPerSimd<NL, NH, MIP>))
-decode_binned_reg(const DecodeArgs a) {
-  using S = Shape<NL, CH, PE, HID>;
-  using N = Net<NL, CH, PE, HID, NH>;
-  constexpr bool AHEAD = kTapsAhead<NL, CH, PE, HID, NH, MIP>;
-  constexpr bool WIDE = kWideRows<STORE>;
-  __shared__ __attribute__((aligned(16))) float biases[kRegWaves<NL, NH, MIP>][N::kBiases];
-  const uint32_t lane = lane_id();
-  const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-  const uint32_t nw = blockDim.x / kWave;  // waves of this workgroup, at most kRegWaves
-  const uint32_t D = (uint32_t)a.n_decoders;
-  const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
-  // tiles of the permutation; never more than the buffer holds
-  const uint64_t slots = min((uint64_t)bin_off(a, D), a.perm_capacity);
-  const uint32_t total_tiles = (uint32_t)(slots / kWave);
-  const uint32_t blk = xcd_local_block(blockIdx.x, gridDim.x);
-  const uint32_t t0 = (uint32_t)((uint64_t)total_tiles * blk / gridDim.x);
-  const uint32_t t_end = (uint32_t)((uint64_t)total_tiles * (blk + 1) / gridDim.x);
-  // the first four tiles of every wave are fixed (the pipeline starts with them)
-  __shared__ uint32_t dealt;
-  if (threadIdx.x == 0) dealt = 4 * nw;
-  __syncthreads();
-  if (t0 + w >= t_end) return;
-  // A tile of this wave and its bin: tiles at or past `be` belong to later bins.
-  struct Cursor {
-    uint32_t t, d, be;
-  };
-  auto seek = [&](Cursor c, uint32_t t) -> Cursor {
-    c.t = t;
-    while (t >= c.be && c.d + 1 < D) {
-      ++c.d;
-      c.be = bin_off(a, c.d + 1) / kWave;
-    }
-    return c;
-  };
-  Cursor c0;
-  c0.t = t0 + w;
-  c0.d = bin_of_slot(a, D, c0.t * kWave);
-  c0.be = bin_off(a, c0.d + 1) / kWave;
-  Cursor c1 = seek(c0, c0.t + nw), c2 = seek(c1, c1.t + nw), c3 = seek(c2, c2.t + nw);
-  // perm entry of this wave's slot in a tile.  The load is unconditional (slot
-  // 0 exists whenever there is a tile) and the entry stays raw until it is
-  // used, with `has` saying whether the tile is in the range: selecting right
-  // after the load would wait for it.
-  struct Slot {
-    uint32_t raw;
-    bool has;
-  };
-  auto slot_query = [&](const Cursor &c) -> Slot {
-    const bool has = c.t < t_end;
-    return Slot{a.perm[has ? c.t * kWave + lane : 0u], has};
-  };
-  // Software pipeline.  Vector-memory operations complete in issue order as
-  // far as the wait counter is concerned, and stores count too, so the order
-  // in tile k is: taps of tile k+1, (after the MLP) query data of tile k+2,
-  // permutation entry of tile k+3, and only then the stores of tile k.
-  RegNet<NL, CH, PE, HID, NH> net;
-  net.lds = biases[w];
-  const Slot s0 = slot_query(c0);
-  const Slot s1 = slot_query(c1);
-  Slot p_next = slot_query(c2);  // tile 2
-  Query cur = load_query<NL, MIP>(a, s0.raw, s0.has);
-  Query q_next = load_query<NL, MIP>(a, s1.raw, s1.has);  // tile 1
-  __builtin_amdgcn_sched_barrier(0);
-  net.load(a, c0.d);
-  uint32_t held = c0.d;
-  cur = validate(a, cur);  // tile 0
-  TileTaps<NL, CH> taps;
-  if constexpr (AHEAD) fetch_taps<NL, CH>(a, cur, taps);
-  __builtin_amdgcn_sched_barrier(0);
-  // One tile: decode `cur` (taps already in flight), fetch the next tile's taps
-  // from q_in (its query data), load the next tile's decoder if it changes,
-  // prefetch query data of the tile after from p_in into q_out and the
-  // permutation entry of the tile after that into p_out, then store.
-  auto tile = [&](const Query &q_in, const Slot &p_in, Query &q_out, Slot &p_out) {
-    uint32_t next = 0;
-    if (lane == 0) next = atomicAdd(&dealt, 1u);
-    uint32_t x[S::F / 2];
-    if constexpr (AHEAD) {
-      interp_taps<NL, CH, PE>(taps, x);
-      if constexpr (PE > 0) pos_encoding<PE>(cur.u, cur.v, x + NL * CH / 2);
-    } else {
-      gather<NL, CH, PE, MIP>(a, cur, x);
-    }
-    const Query nxt = validate(a, q_in);
-    if constexpr (AHEAD) fetch_taps<NL, CH>(a, nxt, taps);
-    half8 xb[4][S::KS0];
-    to_b16<S::KS0, S::F / 2>(x, xb);
-    floatx4 y[4];
-    mlp<NL, CH, PE, HID, NH, LEAKY>(net, xb, y, a.slope_h2);
-    const TileOut<WIDE> o = finish16<WIDE>(y, net.biases() + HID * (1 + NH), cur.q, cur.valid);
-    __builtin_amdgcn_sched_barrier(0);
-    if (c1.t < t_end && c1.d != held) {
-      net.load(a, c1.d);
-      held = c1.d;
-    }
-    __builtin_amdgcn_sched_barrier(0);
-    q_out = load_query<NL, MIP>(a, p_in.raw, p_in.has);
-    p_out = slot_query(c3);
-    __builtin_amdgcn_sched_barrier(0);
-    store_out16<STORE, WIDE>(out_rsrc, a.out_dim, o, a.out_f16);
-    cur = nxt;
-    c0 = c1;
-    c1 = c2;
-    c2 = c3;
-    c3 = seek(c3, t0 + __builtin_amdgcn_readfirstlane(next));
-  };
-  // Unrolled by two with the prefetch registers swapping roles, so a fetched
-  // value is never copied between registers (a copy would wait for the fetch).
-  Query q_b;
-  Slot p_b;
-  for (;;) {
-    tile(q_next, p_next, q_b, p_b);
-    if (c0.t >= t_end) break;
-    tile(q_b, p_b, q_next, p_next);
-    if (c0.t >= t_end) break;
-  }
-}
-
-// Binned decode with the weights in LDS (128-wide decoders): a workgroup walks
-// a contiguous range of tiles, up to eight at a time inside one bin, restaging
-// the decoder when the bin changes.
-template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
-__global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a) {
+__global__ void __launch_bounds__(kThreads, kBinnedWavesPerSimd<HID>)
+decode_binned(const DecodeArgs a, uint32_t split) {
   using S = Shape<NL, CH, PE, HID>;
   using N = Net<NL, CH, PE, HID, NH>;
   constexpr bool WIDE = kWideRows<STORE>;
+  constexpr bool AHEAD = kBinnedTapsAhead<HID, MIP>;
   extern __shared__ __attribute__((aligned(16))) uint32_t lds[];
   const uint32_t lane = lane_id();
   const uint32_t w = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
@@ -1060,19 +940,31 @@ __global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a)
   const __amdgpu_buffer_rsrc_t out_rsrc = out_resource(a);
   const uint64_t slots = min((uint64_t)bin_off(a, D), a.perm_capacity);
   const uint32_t total_tiles = (uint32_t)(slots / kWave);
-  const uint32_t per = (total_tiles + gridDim.x - 1) / gridDim.x;
-  const uint32_t t = xcd_local_block(blockIdx.x, gridDim.x) * per;
-  const uint32_t t_end = min(t + per, total_tiles);
+  uint32_t t, t_end;
+  if (split) {
+    const uint32_t half = gridDim.x / 16, xcd = blockIdx.x % 8, j = blockIdx.x / 8;
+    const uint64_t w0 = (uint64_t)xcd * half * 3 + (j < half ? 2 * j : half + j);
+    const uint64_t w1 = w0 + (j < half ? 2 : 1), parts = (uint64_t)gridDim.x / 2 * 3;
+    t = (uint32_t)(total_tiles * w0 / parts);
+    t_end = (uint32_t)(total_tiles * w1 / parts);
+  } else {
+    const uint32_t per = (total_tiles + gridDim.x - 1) / gridDim.x;
+    t = xcd_local_block(blockIdx.x, gridDim.x) * per;
+    t_end = min(t + per, total_tiles);
+  }
   if (t >= t_end) return;
   const uint32_t first = bin_of_slot(a, D, t * kWave);
-  // Tiles go in weighted groups of consecutive tiles of one bin, tile t + w to
-  // wave w; every wave walks the same (uniform) sequence of groups.  A wave
+  // Tiles go in (128-wide: weighted) groups of consecutive tiles of one bin, tile
+  // t + w to wave w; every wave walks the same (uniform) sequence of groups.  A wave
   // without a tile in a group skips its MLP and stores but still takes part in
   // its staging and prefetches.
+  auto next = [&](const Group &g) {
+    return HID > 64 ? next_wgroup<kWaves>(a, g, D, t_end) : next_group<kWaves>(a, g, D, t_end);
+  };
   Group g0 = group_at<kWaves>(a, t, first, bin_off(a, first + 1) / kWave, D, t_end);
-  Group g1 = next_wgroup<kWaves>(a, g0, D, t_end);
-  Group g2 = next_wgroup<kWaves>(a, g1, D, t_end);
-  Group g3 = next_wgroup<kWaves>(a, g2, D, t_end);
+  Group g1 = next(g0);
+  Group g2 = next(g1);
+  Group g3 = next(g2);
   struct Slot {
     uint32_t raw;
     bool has;
@@ -1093,7 +985,7 @@ __global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a)
   restage(g0.d);
   uint32_t staged = g0.d;
   TileTaps<NL, CH> taps;
-  if constexpr (!MIP) fetch_taps<NL, CH>(a, cur, taps);
+  if constexpr (AHEAD) fetch_taps<NL, CH>(a, cur, taps);
   __builtin_amdgcn_sched_barrier(0);
   const Slot s1 = slot_query(g1);
   Query q_next = load_query<NL, MIP>(a, s1.raw, s1.has);  // tile 1
@@ -1111,7 +1003,7 @@ __global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a)
     TileOut<WIDE> o;
     if (busy) {
       uint32_t x[S::F / 2];
-      if constexpr (MIP) {
+      if constexpr (!AHEAD) {
         gather<NL, CH, PE, MIP>(a, cur, x);
       } else {
         interp_taps<NL, CH, PE>(taps, x);
@@ -1132,7 +1024,7 @@ __global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a)
     }
     // next tile: taps, then the prefetches, then this tile's stores
     const Query nxt = validate(a, q_in);
-    if constexpr (!MIP) fetch_taps<NL, CH>(a, nxt, taps);
+    if constexpr (AHEAD) fetch_taps<NL, CH>(a, nxt, taps);
     __builtin_amdgcn_sched_barrier(0);
     q_out = load_query<NL, MIP>(a, p_in.raw, p_in.has);
     p_out = slot_query(g3);
@@ -1142,7 +1034,7 @@ __global__ void __launch_bounds__(kThreads, 1) decode_binned(const DecodeArgs a)
     g0 = g1;
     g1 = g2;
     g2 = g3;
-    g3 = next_wgroup<kWaves>(a, g3, D, t_end);
+    g3 = next(g3);
   };
   Query q_b;
   Slot p_b;
@@ -1180,7 +1072,7 @@ __global__ void __launch_bounds__(kThreads, 2) decode_stream_reg(const DecodeArg
   using S = Shape<NL, CH, PE, HID>;
   using N = Net<NL, CH, PE, HID, NH>;
   using R = RegNet<NL, CH, PE, HID, NH>;
-  constexpr bool AHEAD = kTapsAhead<NL, CH, PE, HID, NH, MIP>;
+  constexpr bool AHEAD = kStreamTapsAhead<NL, CH, PE, HID, NH, MIP>;
   constexpr bool WIDE = kWideRows<STORE>;
   __shared__ __attribute__((aligned(16))) float biases[kWaves][N::kBiases];
   __shared__ uint32_t tags[R::kSlots];

@@ -9,15 +9,22 @@ namespace ntc {
 namespace {
 
 // Workgroups of `fn` that fill the current device at once (one round, no tail
-// of late workgroups).
-inline uint64_t resident_groups(const void *fn, int threads, size_t lds) {
+// of late workgroups); *on_cu: those of one CU.
+inline uint64_t resident_groups(const void *fn, int threads, size_t lds, int *on_cu = nullptr) {
   int dev = 0, cus = 256, per_cu = 0;
   if (hipGetDevice(&dev) == hipSuccess)
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, threads, lds) != hipSuccess ||
       per_cu < 1)
     per_cu = 1;
+  if (on_cu) *on_cu = per_cu;
   return (uint64_t)cus * (uint64_t)per_cu;
+}
+
+// Lets a kernel use more than the default 64 KB of dynamic LDS.
+inline bool allow_lds(const void *fn, size_t lds) {
+  return lds <= 64 * 1024 || hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 (int)lds) == hipSuccess;
 }
 
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>
@@ -31,54 +38,46 @@ int launch_shape(const DecodeArgs &a, hipStream_t stream) {
     return NTC_ERR_UNSUPPORTED;
   }
   const uint64_t tiles = a.bin_offset ? (uint64_t)a.max_tiles : ((uint64_t)a.n + kWave - 1) / kWave;
+  if (tiles == 0) return NTC_OK;
   uint64_t blocks = (tiles + kWaves - 1) / kWaves;
-  if (blocks == 0) return NTC_OK;
-  if constexpr (kRegWeights<HID>) {
-    const void *fn = a.bin_offset
-                         ? (const void *)decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>
-                         : (const void *)decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
-    const uint64_t widest = a.bin_offset ? kRegWaves<NL, NH, MIP> : kWaves;
-    const uint64_t cap = resident_groups(fn, (int)widest * kWave, 0);  // workgroups of that width
-    // Waves share nothing but the deal of tiles, so a call that does not fill the
-    // chip takes narrower workgroups and reaches every CU (65,536 queries: 129
-    // workgroups of 8 waves sit on half of the 256 CUs).
-    uint64_t waves = widest;
+  const uint32_t image_bytes = ((uint32_t)N::kImageBytes + 15u) & ~15u;
+  if (a.bin_offset) {
+    const void *fn = (const void *)decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
+    if (!allow_lds(fn, image_bytes)) return NTC_ERR_HIP;
+    int on_cu = 0;
+    const uint64_t cap = resident_groups(fn, kThreads, image_bytes, &on_cu);
+    if (blocks > cap) blocks = cap;
+    // two workgroups on every CU (the grid a multiple of 16)
+    const bool split = on_cu == 2 && blocks == cap && blocks % 16 == 0;
+    hipLaunchKernelGGL((decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
+                       dim3((unsigned)blocks), dim3(kThreads), image_bytes, stream, a,
+                       split ? 1u : 0u);
+  } else if constexpr (kRegWeights<HID>) {
+    const void *fn = (const void *)decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
+    const uint64_t cap = resident_groups(fn, kThreads, 0);  // workgroups of kWaves
+    // Waves share nothing but the decoder cache, so a call that does not fill the
+    // chip takes narrower workgroups, without one, and reaches every CU (65,536
+    // queries: 128 workgroups of 8 waves sit on half of the 256 CUs).
+    uint64_t waves = kWaves;
     while (waves > 1 && tiles <= cap * waves / 2) waves /= 2;
     blocks = (tiles + waves - 1) / waves;
-    if (blocks > cap * (widest / waves)) blocks = cap * (widest / waves);
-    const dim3 grid((unsigned)blocks), threads((unsigned)waves * kWave);
-    if (a.bin_offset) {
-      hipLaunchKernelGGL((decode_binned_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
-                         0, stream, a);
-    } else {
-      // the decoder cache takes a CU's LDS, so it goes with the widest workgroups
-      // (one per CU anyway) and pays only where there is a decoder to switch to
-      using R = RegNet<NL, CH, PE, HID, NH>;
-      const bool cached = waves == kWaves && a.n_decoders > 1;
-      const size_t lds = cached ? (size_t)R::kSlots * N::kImageBytes : 0;
-      if (cached &&
-          hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return NTC_ERR_HIP;
-      hipLaunchKernelGGL((decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>), grid, threads,
-                         lds, stream, a, cached ? 1u : 0u);
-    }
+    if (blocks > cap * (kWaves / waves)) blocks = cap * (kWaves / waves);
+    // the decoder cache takes a CU's LDS, so it goes with the widest workgroups
+    // (one per CU anyway) and pays only where there is a decoder to switch to
+    const bool cached = waves == kWaves && a.n_decoders > 1;
+    const size_t lds = cached ? (size_t)RegNet<NL, CH, PE, HID, NH>::kSlots * N::kImageBytes : 0;
+    if (!allow_lds(fn, lds)) return NTC_ERR_HIP;
+    hipLaunchKernelGGL((decode_stream_reg<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
+                       dim3((unsigned)blocks), dim3((unsigned)waves * kWave), lds, stream, a,
+                       cached ? 1u : 0u);
   } else {
-    const uint32_t image_bytes = ((uint32_t)N::kImageBytes + 15u) & ~15u;
-    const void *fn = a.bin_offset
-                         ? (const void *)decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>
-                         : (const void *)decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
-    const size_t lds = image_bytes + (a.bin_offset ? 0 : kWaves * N::kBiases * sizeof(float));
-    if (lds > 64 * 1024 &&
-        hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-      return NTC_ERR_HIP;
+    const void *fn = (const void *)decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>;
+    const size_t lds = image_bytes + kWaves * N::kBiases * sizeof(float);
+    if (!allow_lds(fn, lds)) return NTC_ERR_HIP;
     const uint64_t cap = resident_groups(fn, kThreads, lds);
     if (blocks > cap) blocks = cap;
-    if (a.bin_offset)
-      hipLaunchKernelGGL((decode_binned<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
-                         dim3((unsigned)blocks), dim3(kThreads), lds, stream, a);
-    else
-      hipLaunchKernelGGL((decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
-                         dim3((unsigned)blocks), dim3(kThreads), lds, stream, a, image_bytes);
+    hipLaunchKernelGGL((decode_stream_mixed<NL, CH, PE, HID, NH, MIP, STORE, LEAKY>),
+                       dim3((unsigned)blocks), dim3(kThreads), lds, stream, a, image_bytes);
   }
   return hip_status(hipGetLastError());
 }

@@ -1,7 +1,7 @@
 """GPU parity of the decode where its weight forms, workgroup widths and tile deals
-change: weights in registers or in LDS, taps ahead of the MLP or gathered in
-place, decoder blocks at odd offsets (an odd output width), calls that fill a
-fraction of the chip up to several tiles per wave, and non-finite latents.
+change: weights in registers (64-wide, stream order) or in LDS, taps ahead of the
+MLP or gathered in place, decoder blocks at odd offsets (an odd output width), calls
+that fill a fraction of the chip up to several tiles per wave, and non-finite latents.
 
 Tolerance 2e-3 (max-abs on channels in [0, 1]): fp16 operands and activations,
 fp32 accumulation, as everywhere in the decode tests.
@@ -70,9 +70,9 @@ def test_weight_forms(dev, oracle, levels, ch, hid, nh, out, octaves, mip):
 @pytest.mark.parametrize("tiles", [1, 3, 255, 256, 257, 513, 1025, 2049, 8 * 1024 + 9])
 @pytest.mark.parametrize("D", [1, 3, 70])
 def test_workgroup_widths_and_deal(dev, oracle, tiles, D):
-    """Around the tile counts where the workgroups get wider, and past four tiles
-    a wave (the counter deals), with one decoder, few, and more than one probe
-    round of the bin search."""
+    """Around the tile counts where the stream decode's workgroups get wider, up to
+    several tiles a wave, with one decoder, few, and more than one probe round of the
+    bin search."""
     n = tiles * 64 - 17
     w = workload(tiles + D, n, 2, 8, 64, 1, 4, 0, False, T=80, D=D)
     print(f"[deal] n={n} D={D}", file=sys.stderr, flush=True)
@@ -80,6 +80,23 @@ def test_workgroup_widths_and_deal(dev, oracle, tiles, D):
     pick = np.unique(np.linspace(0, n - 1, min(n, 4000)).astype(np.int64))
     part = W.Workload("part", w.n_textures, w.res, w.channels, w.latents, D, w.dims, w.params,
                       w.tex_to_dec, w.tex_id[pick].copy(), w.uv[pick].copy(), None)
+    assert np.abs(got[pick] - oracle.decode(part)).max() <= TOL
+
+
+@pytest.mark.parametrize("tiles", [4090, 4096, 4099, 8197])
+@pytest.mark.parametrize("D,T,nh,mip", [(1, 1, 1, False), (40, 7, 1, True), (9, 9, 2, False)])
+def test_binned_ranges_of_two_workgroups_a_cu(dev, oracle, tiles, D, T, nh, mip):
+    """Around the size from which every CU has two full workgroups, whose ranges of
+    tiles are then unequal: every row written once, with the stream decode's bits,
+    over bins without queries (7 textures of 40 decoders) too."""
+    n = tiles * 64 - 13
+    w = workload(tiles + D, n, 2, 16, 64, nh, 8, 0, mip, T=T, D=D)
+    print(f"[two-groups] tiles={tiles} D={D} nh={nh} mip={mip}", file=sys.stderr, flush=True)
+    got = both(dev, w).cpu().numpy()
+    pick = np.unique(np.linspace(0, n - 1, 4000).astype(np.int64))
+    part = W.Workload("part", w.n_textures, w.res, w.channels, w.latents, D, w.dims, w.params,
+                      w.tex_to_dec, w.tex_id[pick].copy(), w.uv[pick].copy(),
+                      w.mip[pick].copy() if mip else None)
     assert np.abs(got[pick] - oracle.decode(part)).max() <= TOL
 
 

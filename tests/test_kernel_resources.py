@@ -2,6 +2,7 @@
 (paper_2608_27888_amd/libntc.kernels.json, written by the build): the launch shapes
 count on the occupancy, and a spilled register is memory traffic inside a loop."""
 import json
+import re
 
 import pytest
 
@@ -52,3 +53,28 @@ def test_binning_runs_eight_waves_a_simd_without_scratch(kernels):
         for name, used in named(kernels, part).items():
             assert used["ScratchSize"] == 0, (name, used)
             assert used["Occupancy"] == 8, (name, used)
+
+
+def decode(kernels, kernel, **shape):
+    """Decode kernels by their template arguments."""
+    pattern = re.compile(kernel + r"ILi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELi(\d+)ELb(\d)ELi(\d)ELb(\d)E")
+    names = ("levels", "channels", "pe", "hidden", "hidden_layers", "mip", "store", "leaky")
+    found = {}
+    for k, v in kernels.items():
+        m = pattern.search(k)
+        if m:
+            args = dict(zip(names, map(int, m.groups())))
+            if all(args[n] == want for n, want in shape.items()):
+                found[k] = (args, v)
+    assert found, (kernel, shape)
+    return found
+
+
+def test_binned_decode_of_64_wide_runs_four_waves_a_simd(kernels):
+    """Two waves a SIMD were slower on most shapes.  At four, decoders with two hidden
+    layers or a positional encoding may spill a little; the plain ones may not."""
+    for name, (args, used) in decode(kernels, "decode_binned", hidden=64).items():
+        assert used["Occupancy"] >= 4, (name, used)
+        assert used["ScratchSize"] <= 64, (name, used)
+        if args["hidden_layers"] == 1 and args["pe"] == 0 and args["levels"] == 2:
+            assert used["ScratchSize"] == 0, (name, used)
