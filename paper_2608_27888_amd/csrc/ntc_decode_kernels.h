@@ -908,11 +908,13 @@ constexpr bool kRegWeights = HID == 64;
 // Taps ahead.  Stream: the taps of the next tile are fetched before this tile's MLP
 // where they and the weights leave it its registers: up to 64 registers of taps (2
 // levels of 16 channels) and 18 fragments.  Otherwise a tile gathers when it starts:
-// carrying 3 levels' taps (96 registers) beside the weights spilled (1080p frame of
-// 48-64-64-8: 147 us against 83).
+// carrying 3 levels' taps (96 registers) beside the weights spilled, as did 64 and a
+// positional encoding (1080p frame of 16 decoders, 4 octaves 136 us against 103
+// gathered in place, 8 octaves 140 against 114; 2 x 8 channels with 8 octaves fit, 94
+// against 98).
 template <int NL, int CH, int PE, int HID, int NH, bool MIP>
 constexpr bool kStreamTapsAhead =
-    kRegWeights<HID> && !MIP && NL * CH <= 32 &&
+    kRegWeights<HID> && !MIP && NL * CH <= (PE > 0 ? 16 : 32) &&
     Net<NL, CH, PE, HID, NH>::kFrags <= 18;
 // Binned: fetched before this tile's stores for 128-wide decoders; with four waves a
 // SIMD the other waves hide a gather at the tile's start (1080p one material, passes

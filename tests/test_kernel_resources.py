@@ -78,3 +78,13 @@ def test_binned_decode_of_64_wide_runs_four_waves_a_simd(kernels):
         assert used["ScratchSize"] <= 64, (name, used)
         if args["hidden_layers"] == 1 and args["pe"] == 0 and args["levels"] == 2:
             assert used["ScratchSize"] == 0, (name, used)
+
+
+def test_stream_decode_of_64_wide_holds_its_weights(kernels):
+    """No scratch beside the weights in registers, but for the largest decoder (3 x 16
+    channels, two hidden layers, 26 fragments) and one store form of 2 x 8 channels
+    with 8 octaves."""
+    for name, (args, used) in decode(kernels, "decode_stream_reg", hidden=64).items():
+        largest = args["levels"] == 3 and args["hidden_layers"] == 2
+        octaves = args["channels"] == 8 and args["pe"] == 32
+        assert used["ScratchSize"] <= (52 if largest else 8 if octaves else 0), (name, used)
