@@ -12,13 +12,23 @@
 // exactly).  What bounds it: the written rows (64 bytes a query at 2 x 16 fp16
 // channels) and the L1's tap traffic.  Storing each lane's own row, 16 bytes
 // every 64 or more, touched 32 lines an instruction: 67.4 us for the 1080p frame's fp16
-// rows; through LDS, non-temporal, 31.0 us (fp32 rows 111 -> 49 us).
+// rows; through LDS 32.5 us (fp32 rows, non-temporal, 111 -> 49 us).  On inputs read
+// for the first time the taps' way from memory bounds it: 67 -> 50 us.
 #include "ntc_decode_kernels.h"
 
 namespace ntc {
 namespace {
 
-template <int NL, int CH, bool MIP, bool F16>
+// Rows of up to this many bytes are left in the 256 MB last-level cache for whoever
+// reads them next; more are stored past it (non-temporal).  Alone the non-temporal
+// rows are faster, by 1.4 us of 32.7 for 133 MB and by 20 of 70 for 265, but a product
+// of the rows with a 32 x 64 matrix behind the call takes, both together, 475 us
+// against 414 at 133 MB and 323 against 323 at 265, a sum of each row 309 against 282
+// and 325 against 344.
+constexpr uint64_t kCachedRows = (uint64_t)160 << 20;
+
+// NT: non-temporal rows.
+template <int NL, int CH, bool MIP, bool F16, bool NT>
 __global__ void __launch_bounds__(kBlock) gather_rows(const DecodeArgs a) {
   constexpr int F = NL * CH;           // features per row, a multiple of 8
   constexpr int kStride = F / 2 + 4;   // words of an LDS row: odd in 16-byte pieces, so the
@@ -58,7 +68,10 @@ __global__ void __launch_bounds__(kBlock) gather_rows(const DecodeArgs a) {
         const half2v lo = as_h2(h[0]), hi = as_h2(h[1]);
         v = __builtin_bit_cast(u32x4, floatx4{(float)lo[0], (float)lo[1], (float)hi[0], (float)hi[1]});
       }
-      if ((valid >> row) & 1) __builtin_nontemporal_store(v, out + p);
+      if ((valid >> row) & 1) {
+        if constexpr (NT) __builtin_nontemporal_store(v, out + p);
+        else out[p] = v;
+      }
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
@@ -69,8 +82,11 @@ template <int NL, int CH, bool MIP, bool F16>
 int launch_rows(const DecodeArgs &a, hipStream_t stream) {
   uint64_t blocks = ((uint64_t)a.n + kBlock - 1) / kBlock;
   if (blocks > 65536) blocks = 65536;  // grid stride beyond
-  hipLaunchKernelGGL((gather_rows<NL, CH, MIP, F16>), dim3((unsigned)blocks), dim3(kBlock), 0,
-                     stream, a);
+  const dim3 grid((unsigned)blocks), block(kBlock);
+  if ((uint64_t)a.n * (NL * CH * (F16 ? 2 : 4)) <= kCachedRows)
+    hipLaunchKernelGGL((gather_rows<NL, CH, MIP, F16, false>), grid, block, 0, stream, a);
+  else
+    hipLaunchKernelGGL((gather_rows<NL, CH, MIP, F16, true>), grid, block, 0, stream, a);
   return hip_status(hipGetLastError());
 }
 

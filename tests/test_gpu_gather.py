@@ -102,3 +102,23 @@ def test_gather_ragged_sizes_and_invalid_rows(dev, n):
     o = out.cpu().numpy()
     assert np.all(o[bad] == 7.25)
     assert np.array_equal(o[~bad], full[:n].cpu().numpy()[~bad])
+
+
+@pytest.mark.parametrize("dtype,n", [(torch.float32, 873_813), (torch.float32, 873_814),
+                                     (torch.float16, 1_747_626), (torch.float16, 1_747_627)])
+def test_gather_rows_of_any_size(dev, dtype, n):
+    """Around 160 MiB of rows (3 levels of 16 channels), where they stop being left in
+    the cache: the rows of a repeated stream repeat, bit for bit, invalid ones stay."""
+    w = W.small("wide_trilinear")
+    model, q = ntc.upload(w, dev)
+    few = ntc.gather_features(model, q, out_dtype=dtype)
+    pick = torch.arange(n, device=dev) % w.n
+    tex = q.tex_id[pick]
+    bad = torch.arange(n, device=dev) % 1009 == 7
+    tex[bad] = w.n_textures
+    say(f"[gather-size] {dtype} n={n}")
+    out = torch.full((n, sum(w.channels)), 7.25, dtype=dtype, device=dev)
+    ntc.gather_features(model, ntc.DeviceQueries(tex, q.uv[pick].contiguous(), q.mip[pick]), out,
+                        dtype)
+    assert torch.equal(out[~bad], few[pick][~bad])
+    assert bool((out[bad] == 7.25).all())
