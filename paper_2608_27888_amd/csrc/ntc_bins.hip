@@ -134,7 +134,8 @@ __device__ __forceinline__ void load_batch(const uint32_t *__restrict__ tex_id,
 // matched (65,536 random queries of 2 decoders: 13.7 -> 11.7 us; 4K frames of regions
 // are within 2 % of peeling: 27.0 us against 26.4 with two decoders, 29.1 against 28.5
 // with four, where a peeled first row that decides takes 29.4 and 31.0); with 5 to 16
-// every row is peeled (the choice alone cost the 4K clustered frame 2 us).
+// every row is peeled (the choice alone cost the 4K clustered frame 2 us; 8x8 tiles of
+// 16 decoders take 27.6 us at 1080p and 54.6 at 4K so, as before rows were matched).
 constexpr uint32_t kPeelMost = 4;
 
 // Lanes of `valid` whose value equals v, compared in its low B bits; v may differ

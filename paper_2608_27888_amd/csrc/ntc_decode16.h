@@ -21,8 +21,9 @@
 // Selected with NTC_GATHER_STAGED for binned decode without mip blending.  On
 // MI355X it is slower than the direct gather of ntc_decode_kernels.h: the
 // planning (leaders, slots, the exchange of quad addresses) adds about 40 VALU
-// instructions per tile, more than the 8-10 % of decode time that tap loads
-// cost there.
+// instructions per tile, and its plan and prefetches keep it at three waves per
+// SIMD (pass over the 4K frame of 16 decoders 213 us against 185, over a 1080p one
+// 75 against 61).
 #pragma once
 
 #include "ntc_decode_kernels.h"
@@ -203,11 +204,12 @@ __device__ __forceinline__ void gather_staged(const DecodeArgs &a, const Query &
 
 // ----------------------------------------------------------------- kernel
 
-// Waves per workgroup and per SIMD of the 16x16 binned kernel.  A wave holds
-// the MLP's activations, the next tile's plan and the query prefetches in at
-// most 168 VGPRs (3 waves per SIMD) for 64-wide decoders: one 12-wave
-// workgroup per CU shares one staged decoder.  128-wide decoders use 8-wave
-// workgroups, 2 waves per SIMD.
+// Waves per workgroup and per SIMD of the 16x16 binned kernel.  64-wide decoders: one
+// 12-wave workgroup per CU shares one staged decoder.  The MLP's activations, the next
+// tile's plan and the query prefetches don't all fit the 168 VGPRs of three waves per
+// SIMD (most forms spill 12-88 bytes a lane); two waves per SIMD spill nothing, but
+// the 4K frame takes 222 us against 213 (1080p 74 against 75, two hidden layers 84
+// against 88).  128-wide decoders use 8-wave workgroups, 2 waves per SIMD.
 template <int HID>
 constexpr int kWaves16 = HID > 64 ? 8 : 12;
 template <int HID>

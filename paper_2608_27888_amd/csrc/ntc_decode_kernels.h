@@ -24,11 +24,12 @@
 // are the accumulator input of the first MFMA of each row block.  Every kernel
 // runs this one function (mlp), so binned and stream mode give the same bits.
 //
-// Why 16x16x32: the decode's time follows the work of a tile (its clock is 1.7-1.9
-// GHz by wave timestamps, 2.1 without its MFMAs or its LDS weight reads).  16x16x32
-// moves half the accumulator bytes per flop of 32x32x16 and pads an 8-wide output
-// layer to 16 rows instead of 32: 161 -> 153 us on the 4K clustered frame, 50.7 -> 48
-// us on the 1080p one.
+// What bounds it: issue.  On the 4K clustered frame a tile takes 56 MFMAs (35 % of the
+// SIMD's cycles) and 339 other vector instructions (53 % at one per 4 cycles), and the
+// waves wait on a dependency or counter for 52 % of theirs (SQ counters).
+// Why 16x16x32: it moves half the accumulator bytes per flop of 32x32x16 and pads an
+// 8-wide output layer to 16 rows instead of 32: 161 -> 153 us on the 4K clustered
+// frame, 50.7 -> 48 us on the 1080p one.
 //
 // Binned, a workgroup stages its decoder in LDS and every wave reads the fragments
 // there: four waves per SIMD for 64-wide decoders (LDS image about 15 KB), two for
@@ -213,7 +214,9 @@ struct RegNet : Net<NL, CH, PE, HID, NH> {
   // A workgroup's LDS cache of decoders (stream mode): kSlots images, decoder d
   // in slot d % kSlots, filled once by the first wave that misses there and
   // never replaced, so a filled slot is read without a lock and no wave waits
-  // for another.  A tag is kEmpty, kFilling or the decoder + 1.
+  // for another.  Of decoders that share a slot, the one that a wave came to first
+  // is read from LDS and the others from memory for the whole call.  A tag is
+  // kEmpty, kFilling or the decoder + 1.
   static constexpr uint32_t kSlots = (uint32_t)(kCacheBytes / N::kImageBytes);
   static constexpr uint32_t kEmpty = 0u, kFilling = 0xFFFFFFFFu;
   __device__ __forceinline__ void load_cached(const DecodeArgs &a, uint32_t dec, uint32_t *tags,
@@ -1146,7 +1149,10 @@ __global__ void __launch_bounds__(kThreads, 2) decode_stream_reg(const DecodeArg
 // MFMA A fragment straight from that decoder's parameter block, with no
 // restaging and no barrier.  Restaging the union of a group's decoders in LDS
 // would make every wave wait for every decoder of the group; per-wave reads
-// alone are twice as slow as one staged copy when waves share a decoder.
+// alone are twice as slow as one staged copy when waves share a decoder.  1080p frame
+// of 16 decoders: 48-128-128-128-8 1201 us (1506 with 32x32x16 MFMAs), 32-128-128-8
+// 605 (662).  With two hidden layers the per-wave path spills 130-310 bytes a lane
+// (210-330 before); it waits for its fragments from memory in any case.
 constexpr uint32_t kStreamVoteEvery = 8;
 
 template <int NL, int CH, int PE, int HID, int NH, bool MIP, int STORE, bool LEAKY>

@@ -12,20 +12,21 @@
 // exactly).  What bounds it: the written rows (64 bytes a query at 2 x 16 fp16
 // channels) and the L1's tap traffic.  Storing each lane's own row, 16 bytes
 // every 64 or more, touched 32 lines an instruction: 67.4 us for the 1080p frame's fp16
-// rows; through LDS 32.5 us (fp32 rows, non-temporal, 111 -> 49 us).  On inputs read
-// for the first time the taps' way from memory bounds it: 67 -> 50 us.
+// rows; through LDS, non-temporal, 31.4 us (fp32 rows 111 -> 50).  On inputs read for the
+// first time the taps' way from memory bounds it: 67 -> 53.6 us.
 #include "ntc_decode_kernels.h"
 
 namespace ntc {
 namespace {
 
-// Rows of up to this many bytes are left in the 256 MB last-level cache for whoever
-// reads them next; more are stored past it (non-temporal).  Alone the non-temporal
-// rows are faster, by 1.4 us of 32.7 for 133 MB and by 20 of 70 for 265, but a product
-// of the rows with a 32 x 64 matrix behind the call takes, both together, 475 us
-// against 414 at 133 MB and 323 against 323 at 265, a sum of each row 309 against 282
-// and 325 against 344.
-constexpr uint64_t kCachedRows = (uint64_t)160 << 20;
+// Rows of up to this many bytes (half of the eight L2s) are left in the caches for
+// whoever reads them next: as fast alone (9.2 us for 262,144 fp16 rows) and with a
+// product of the rows with a 32 x 64 matrix behind it 52.7 us against 59.3.  More are
+// stored past the caches (non-temporal).  Their reader pays for it, 475 us against 414
+// for a 1080p frame's 133 MB and that product, but the gather alone takes 31.4 us
+// against 51.8 where calls alternate between buffers (32.6 into one), 50 against 70
+// for 265 MB.
+constexpr uint64_t kCachedRows = (uint64_t)16 << 20;
 
 // NT: non-temporal rows.
 template <int NL, int CH, bool MIP, bool F16, bool NT>

@@ -104,11 +104,11 @@ def test_gather_ragged_sizes_and_invalid_rows(dev, n):
     assert np.array_equal(o[~bad], full[:n].cpu().numpy()[~bad])
 
 
-@pytest.mark.parametrize("dtype,n", [(torch.float32, 873_813), (torch.float32, 873_814),
-                                     (torch.float16, 1_747_626), (torch.float16, 1_747_627)])
+@pytest.mark.parametrize("dtype,n", [(torch.float32, 87_381), (torch.float32, 87_382),
+                                     (torch.float16, 174_762), (torch.float16, 174_763)])
 def test_gather_rows_of_any_size(dev, dtype, n):
-    """Around 160 MiB of rows (3 levels of 16 channels), where they stop being left in
-    the cache: the rows of a repeated stream repeat, bit for bit, invalid ones stay."""
+    """Around 16 MiB of rows (3 levels of 16 channels), where they stop being left in the
+    caches: the rows of a repeated stream repeat, bit for bit, invalid ones stay."""
     w = W.small("wide_trilinear")
     model, q = ntc.upload(w, dev)
     few = ntc.gather_features(model, q, out_dtype=dtype)
