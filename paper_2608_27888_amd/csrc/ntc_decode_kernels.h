@@ -946,7 +946,7 @@ decode_binned(const DecodeArgs a, uint32_t split) {
   const uint64_t slots = min((uint64_t)bin_off(a, D), a.perm_capacity);
   const uint32_t total_tiles = (uint32_t)(slots / kWave);
   uint32_t t, t_end;
-  if (split) {
+  if (HID == 64 && split) {  // 128-wide: one workgroup a CU
     const uint32_t half = gridDim.x / 16, xcd = blockIdx.x % 8, j = blockIdx.x / 8;
     const uint64_t w0 = (uint64_t)xcd * half * 3 + (j < half ? 2 * j : half + j);
     const uint64_t w1 = w0 + (j < half ? 2 : 1), parts = (uint64_t)gridDim.x / 2 * 3;
