@@ -132,7 +132,7 @@ __device__ __forceinline__ void load_batch(const uint32_t *__restrict__ tex_id,
 // row of a batch of 16 is peeled, and when it held more than kPeelMost decoders
 // the other rows are matched.  With at most 4 decoders (2 bits) every row is
 // matched (65,536 random queries of 2 decoders: 13.7 -> 11.7 us; 4K frames of regions
-// are within 2 % of peeling: 27.0 us against 26.4 with two decoders, 29.1 against 28.5
+// as fast as peeling or 2 % slower: 25.6 us against 26.4 with two decoders, 29.1 against 28.5
 // with four, where a peeled first row that decides takes 29.4 and 31.0); with 5 to 16
 // every row is peeled (the choice alone cost the 4K clustered frame 2 us; 8x8 tiles of
 // 16 decoders take 27.6 us at 1080p and 54.6 at 4K so, as before rows were matched).
@@ -218,11 +218,8 @@ __device__ __forceinline__ uint32_t match_row(uint32_t d, uint32_t &reg, uint32_
     const uint32_t rank = lanes_below(same);
     uint32_t at = 0;
     if constexpr (REG) {
-      // one bit: two lane reads instead of the LDS permutation's latency (4K frame of
-      // two decoders: 28.6 -> 27.0 us)
-      at = B == 0   ? read_lane(reg, 0)
-           : B == 1 ? (d & 1 ? read_lane(reg, 1) : read_lane(reg, 0))
-                    : (uint32_t)__builtin_amdgcn_ds_bpermute((int)(d << 2), (int)reg);
+      at = B == 0 ? read_lane(reg, 0)
+                  : (uint32_t)__builtin_amdgcn_ds_bpermute((int)(d << 2), (int)reg);
       reg += popcount64(row.equal(lane));
     } else {
       uint32_t old = 0;  // the first lane of each decoder reads and advances its value
@@ -242,6 +239,24 @@ __device__ __forceinline__ uint32_t match_row(uint32_t d, uint32_t &reg, uint32_
 template <bool REG, bool RANK, int B, typename Emit>
 __device__ __forceinline__ void batch_rows(const uint32_t (&d)[kBatchRows], uint32_t &reg,
                                            uint32_t *table, uint32_t lane, Emit emit) {
+  if constexpr (REG && B == 1) {
+    // Two decoders (ids 0 and 1): their values in scalar registers.  A row that
+    // reads them from lanes of `reg` waits for the row before: binning and decode of
+    // 41,400 queries 28.1 -> 27.2 us, binning of 2255 x 1273 16.5 -> 15.4, of 4K 26.8 ->
+    // 25.6.
+    uint32_t c0 = read_lane(reg, 0), c1 = read_lane(reg, 1);
+#pragma unroll
+    for (int j = 0; j < kBatchRows; ++j) {
+      const uint64_t zeros = ballot(d[j] == 0), ones = ballot(d[j] == 1);
+      if constexpr (RANK)
+        emit(j, d[j] == 1 ? c1 + lanes_below(ones) : c0 + lanes_below(zeros));
+      c0 += popcount64(zeros);
+      c1 += popcount64(ones);
+      __builtin_amdgcn_sched_barrier(0);  // else the rows' ballots fill the scalar registers
+    }
+    reg = lane == 0 ? c0 : lane == 1 ? c1 : reg;
+    return;
+  }
   constexpr int kFirst = peels(B) && matches(B) ? 1 : 0;
   uint32_t distinct = kPeelMost + 1, unused;
   if constexpr (kFirst) emit(0, peel_row<REG, RANK>(d[0], reg, table, lane, distinct));
@@ -263,9 +278,10 @@ __device__ __forceinline__ void batch_rows(const uint32_t (&d)[kBatchRows], uint
 // REG: register tables (n_decoders <= 64).  tot (REG only): the workgroup's
 // sums over its waves, column b of tot[n_decoders + 1][gridDim.x], with hist
 // holding each wave's exclusive prefix over the workgroup's waves; NULL: hist
-// holds each wave's own counts.
+// holds each wave's own counts.  Eight waves per SIMD, asked for: with two decoders the
+// rows' masks would take 106 scalar registers (4K frame 26.7 us, 25.6 at 78).
 template <bool REG, int WAVES, int B>
-__global__ void __launch_bounds__(WAVES * kWave)
+__global__ void __launch_bounds__(WAVES * kWave) __attribute__((amdgpu_waves_per_eu(8)))
 bins_count(const uint32_t *__restrict__ tex_id, uint32_t n,
            const uint32_t *__restrict__ tex_to_dec, uint32_t n_textures, uint32_t n_decoders,
            uint32_t chunk, uint32_t *__restrict__ hist, uint32_t *__restrict__ tot) {

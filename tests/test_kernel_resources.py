@@ -52,6 +52,7 @@ def test_binning_runs_eight_waves_a_simd_without_scratch(kernels):
     for part in ("bins_count", "bins_place"):
         for name, used in named(kernels, part).items():
             assert used["ScratchSize"] == 0, (name, used)
+            assert used["VGPRs"] <= 64, (name, used)
             assert used["Occupancy"] == 8, (name, used)
 
 
